@@ -100,6 +100,7 @@ struct del_ctx {
   int prows = 0;    // token rows of a wide prefill pass (0: prefill runs in 16-row passes)
   int hrows = 0;    // rows per layer of the hidden buffer and of the per-row work buffers
   float* rowscale_w = nullptr;   // [hrows] RMS scales of a wide pass
+  float* wide_part = nullptr; size_t wide_part_bytes = 0;   // partial results of a wide GEMM's split k ranges
   char* vct = nullptr; int TcapT = 0; size_t vct_layer_bytes = 0;   // feature-major copy of the values for the
                                                                      // prefill's matrix-core attention (0: off)
   // device memory
@@ -147,7 +148,7 @@ struct del_ctx {
   float t_draft = 0, t_verify = 0, t_shadow = 0;
   int target_waves = 3072;
   int rows_form = 0;          // one-row GEMV: 1 = one row block per work-group for every matrix (DEL_ROWS_FORM)
-  int wide_form = 0;          // prefill GEMMs: 1 = the two-stage form for every matrix (DEL_WIDE_FORM)
+  int wide_form = 0;          // prefill GEMMs: 1 = no k range is split over work-groups (DEL_WIDE_FORM)
   int head_form = 4;          // shadow-head kernel: 4 = register-blocked, 1 = one row block per wave (DEL_HEAD_FORM)
   // Optional (DEL_GRAPHS=1): the segments of a round are captured once per (kind, E, gamma) into HIP
   // graphs and replayed; positions and token ids live in device memory, so a graph depends on
@@ -449,6 +450,7 @@ del_status run_layer_wide(del_ctx* ctx, int l, int m, bool chained) {
   auto wide = [&](GemmP& p, int epi) -> del_status {
     p.M = m;
     p.wide_form = ctx->wide_form;
+    p.part = ctx->wide_part; p.part_bytes = ctx->wide_part_bytes;
     const int pr = prof_begin(ctx, 3, epi, m, (int64_t)p.NB * p.KT * 1024);
     if (pr >= 0) { p.ev_start = ctx->prof_ev[2 * pr]; p.ev_stop = ctx->prof_ev[2 * pr + 1]; }
     HIPCHK(launch_gemm_wide(p, epi, s));
@@ -466,12 +468,14 @@ del_status run_layer_wide(del_ctx* ctx, int l, int m, bool chained) {
   void* Kc = p.Kc; void* Vc = p.Vc;
   void* VcT = ctx->vct ? ctx->vct + (size_t)li * ctx->vct_layer_bytes : nullptr;
   p.VcT = VcT; p.TcapT = ctx->TcapT;
-  if (chained)
-    HIPCHK(launch_rowscale(ctx->ssq_h, ctx->NBd, m, ctx->d, ctx->cfg.rms_eps, ctx->rowscale_w, s));
-  else
+  p.Xs = ctx->xs_h;
+  if (chained) {
+    p.ssq_in = ctx->ssq_h; p.ssq_nb = wide_ssq_nb(ctx->NBd);
+  } else {
     HIPCHK(launch_prep_split(hin, m, m, 0, ctx->dpad, ctx->d, ctx->KTd, ctx->gain_attn(li), 1, ctx->cfg.rms_eps, ctx->xs_h,
                              ctx->rowscale_w, s));
-  p.Xs = ctx->xs_h; p.rowscale = ctx->rowscale_w;
+    p.rowscale = ctx->rowscale_w;
+  }
   if ((st = wide(p, EPI_QKV)) != DEL_OK) return st;
   // 2. causal attention: groups of token rows share the cache reads; then the merge
   AttnP a;
@@ -501,11 +505,10 @@ del_status run_layer_wide(del_ctx* ctx, int l, int m, bool chained) {
   p.ssq_out = ctx->ssq_h1;
   if ((st = wide(p, EPI_RESID)) != DEL_OK) return st;
   // 4. RMSNorm + fused gate/up + SiLU(gate) * up
-  HIPCHK(launch_rowscale(ctx->ssq_h1, ctx->NBd, m, ctx->d, ctx->cfg.rms_eps, ctx->rowscale_w, s));
   p = base_gemm(ctx);
   p.Wt = base + ctx->off_gu; p.NB = ctx->NBgu; p.KT = ctx->KTd; p.N = ctx->NBgu * 16; p.K = ctx->d;
-  p.ACT = ctx->act; p.ldact = ctx->fpad; p.d_ffn = ctx->f;
-  p.Xs = ctx->xs_h1; p.rowscale = ctx->rowscale_w;
+  p.d_ffn = ctx->f;
+  p.Xs = ctx->xs_h1; p.ssq_in = ctx->ssq_h1; p.ssq_nb = wide_ssq_nb(ctx->NBd);
   p.XsOut = ctx->xs_act; p.xs_out_cb_stride = (long long)ctx->KTf * 1024;
   if ((st = wide(p, EPI_SWIGLU)) != DEL_OK) return st;
   // 5. down projection + residual (in place); leaves the next layer's input tiles
@@ -584,7 +587,7 @@ void free_all(del_ctx* c) {
                   c->rope, c->hid, c->q, c->attn, c->act, c->xs_layer, c->xs_shadow, c->rowscale, c->xs_h, c->xs_attn,
                   c->xs_h1, c->xs_act, c->ssq_h, c->ssq_h1, c->PM, c->PL,
                   c->PA, c->pval, c->pidx, c->psum, c->state, c->draft_ids, c->shadow_ids, c->result, c->ids_dev,
-                  c->logits_dbg, c->sink, c->stage, c->slog, c->swf, c->srows, c->unif_dev, c->rowscale_w, c->vct};
+                  c->logits_dbg, c->sink, c->stage, c->slog, c->swf, c->srows, c->unif_dev, c->rowscale_w, c->vct, c->wide_part};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->result_host) (void)hipHostFree(c->result_host);   // conf_host and conf_dev point into the result blocks
@@ -819,6 +822,12 @@ del_status del_create(const del_config* cfg, void* hip_stream, del_ctx** out) {
     CK(dmalloc(&ctx->ssq_h, CBmax * 16 * ctx->NBd * 4));
     CK(dmalloc(&ctx->ssq_h1, CBmax * 16 * ctx->NBd * 4));
     CK(dmalloc(&ctx->rowscale_w, CBmax * 16 * 4));
+    // the workspace that the widest of all passes asks for (a pass may have any number of rows up to prows)
+    const int shapes[4][2] = {{ctx->NBqkv, ctx->KTd}, {ctx->NBd, ctx->KTq}, {ctx->NBgu, ctx->KTd}, {ctx->NBd, ctx->KTf}};
+    for (const auto& sh : shapes)
+      for (int m = 16; m <= ctx->prows; m += 16)
+        ctx->wide_part_bytes = std::max(ctx->wide_part_bytes, wide_part_bytes(wide_plan(sh[0], sh[1], m, ctx->wide_form == 1)));
+    if (ctx->wide_part_bytes) CK(dmalloc(&ctx->wide_part, ctx->wide_part_bytes));
     const char* fl = getenv("DEL_PREFILL_FLASH");
     if (ctx->prows > 0 && (ctx->hd == 64 || ctx->hd == 128) && !(fl && atoi(fl) == 0)) {
       ctx->TcapT = ceil_div(ctx->Tcap, 32) * 32;

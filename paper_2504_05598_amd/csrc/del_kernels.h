@@ -74,8 +74,11 @@ struct GemmP {
   // host side only: when both are set the launch records the kernel's own start and stop
   // timestamps into these events (per-kernel profiling)
   hipEvent_t ev_start, ev_stop;
-  // host side only, wide GEMM: 1 = the two-stage form for every matrix (default 0: the four-deep form where it applies)
+  // wide path, host side: 1 = no matrix's k range is split over work-groups (default 0: where it pays)
   int wide_form;
+  // wide path: workspace for the partial results of split k ranges
+  float* part;
+  size_t part_bytes;
   // host side only, one-row GEMV: 1 = one row block per work-group for every matrix (default 0: several row blocks per
   // work-group where the shape allows)
   int rows_form;
@@ -115,11 +118,19 @@ hipError_t launch_gemm_mfma(const GemmP& p, int epi, int waves, int col_blocks, 
 hipError_t launch_head_gemm(const void* Wt, int NB, int KT, int N, const uint16_t* Xs, int R, const float* rowscale,
                             float* pval, int* pidx, float* psum, int* n_slabs, hipStream_t s,
                             hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, int form = 1);
-// Many token rows at once (prefill): 8 row blocks x up to 256 token rows per work-group, the split
-// activation tiles ([cb][kt] for p.M rows) staged through LDS.  epi: EPI_RESID, EPI_QKV or EPI_SWIGLU.
-hipError_t launch_gemm_wide(const GemmP& p, int epi, hipStream_t s);
-// rowscale[row] = 1 / sqrt(sum_b ssq[row][b] / K + eps) for rows < M.
-hipError_t launch_rowscale(const float* ssq, int nb, int M, int K, float eps, float* rowscale, hipStream_t s);
+// ---- GEMMs over many token rows (del_wide.hip): activations as split tiles [cb][kt] for p.M rows ----
+// How a launch is cut up: tiles of 16 row blocks x CBT blocks of 16 token rows, NCG of them side by side per slab of the
+// matrix; the first `full` tiles run over all k, the other `rem` are split into S ranges of k.
+struct WidePlan {
+  int CBT, NCG, full, rem, S;
+};
+WidePlan wide_plan(int NB, int KT, int M, int whole);   // whole = 1: no splits
+size_t wide_part_bytes(const WidePlan& w);              // workspace a launch with this plan needs (p.part)
+// epi: EPI_RESID (ssq_out: wide_ssq_nb(NB) numbers per token row), EPI_QKV or EPI_SWIGLU (split tiles only).  The RMS
+// scale comes from ssq_in / ssq_nb or from rowscale.
+hipError_t launch_gemm_wide(const GemmP& p, int epi, hipStream_t s);                      // with wide_plan's plan
+hipError_t launch_gemm_wide(const GemmP& p, int epi, const WidePlan& w, hipStream_t s);
+int wide_ssq_nb(int NB);
 hipError_t launch_prep_split(const float* src, int rows, int rows_per_group, int64_t group_stride,
                              int ld, int K, int KT, const float* gain, int rms, float eps,
                              uint16_t* Xs, float* rowscale, hipStream_t s);

@@ -4,23 +4,13 @@
 // cores.  Weights are streamed exactly once per launch in 1 KiB wave-sized tiles (see
 // del_kernels.h); activations stay fp32 on the vector path and are split into bf16 hi + lo
 // halves (16 mantissa bits together) on the matrix-core path, accumulating in fp32.
-#include "del_kernels.h"
+#include "del_device.h"
 #include <hip/hip_ext.h>
 
 namespace del {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
-
 constexpr int MAXW = 16;  // waves per work-group at most
 constexpr int QBMAX = 32;  // query rows per attention batch at most
-
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
 
 template <int KPL> struct WDec;
 template <> struct WDec<8> {  // 8 bf16 in a uint4
@@ -205,12 +195,6 @@ __device__ __forceinline__ void epilogue(const GemmP& p, int nb, float (*fin)[16
 // non-temporal load (no reuse: keeps the stream out of the way of the cached activations),
 // and every wave owns a contiguous span of the k tiles of its row block.
 // ---------------------------------------------------------------------------------------
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint4 ld_stream(const uint4* p) {
-  const u32x4 v = __builtin_nontemporal_load((const u32x4*)p);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 constexpr int GU = 4;  // tiles in flight per wave and pipeline stage (x2: current + next)
 
 // The k tiles of a row block are split over the waves in whole groups of `grp` tiles, as evenly as the
@@ -1216,224 +1200,6 @@ __global__ void __launch_bounds__(512) head_gemm4_k(const uint4* __restrict__ Wt
           if (v > -INFINITY) se += ws[(w * H4_CB + c) * 16 + tk] * expf(v - best);
         }
         psum[(size_t)row * NS + slab] = se;
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------
-// Wide GEMM for passes over many token rows (prefill).  A work-group takes RBW row blocks of the
-// matrix times 8 * CPW blocks of 16 token rows.  The weight tiles of a k tile (RBW KiB) are staged
-// in LDS, double-buffered, and shared by the 8 waves; every wave owns CPW blocks of token rows,
-// whose hi/lo activation tiles it reads straight into registers, so that one weight tile fetched
-// from LDS feeds 2 * CPW matrix instructions.  Work-groups that share a slab of the matrix are
-// given consecutive slots on one XCD (the slab then comes from that XCD's L2 after its first
-// read).  Every wave hands its 16x16 results through a 1 KiB LDS patch of its own to the layer
-// epilogues, block of token rows by block of token rows.
-// ---------------------------------------------------------------------------------------
-template <int EPI, int RBW, int CPW>
-__global__ void __launch_bounds__(512) gemm_wide_k(GemmP p, int NS, int NCG) {
-  extern __shared__ __align__(16) uint4 as[];   // [2][RBW * 64]; reused by the epilogue ([8 waves][256] floats)
-  constexpr int CBW = 8 * CPW;
-  constexpr int AL = RBW * 64 / 512;            // 16-byte pieces of the weight tiles per thread
-  static_assert(RBW * 64 % 512 == 0 && AL >= 1 && RBW * 64 * 2 * 16 >= 8 * 1024, "RBW must be a multiple of 8");
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  // slot -> (slab, group of token-row blocks): the NCG groups of a slab follow each other on one XCD
-  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-  const int cg = local % NCG, slab = (local / NCG) * 8 + xcd;
-  if (slab >= NS) return;
-  const int NB = p.NB, KT = p.KT;
-  const int CB = (p.M + 15) >> 4;
-  const int nb0 = slab * RBW, cb0 = cg * CBW + wave * CPW;
-  const uint4* Wt = (const uint4*)p.Wt;
-  const uint4* Xs = (const uint4*)p.Xs;
-  floatx4 acc[RBW][CPW];
-#pragma unroll
-  for (int r = 0; r < RBW; ++r)
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) acc[r][c] = (floatx4){0.f, 0.f, 0.f, 0.f};
-  // addresses are clamped (row blocks past the matrix, token-row blocks past the pass) so that the
-  // loop has no branches around memory operations; such results are dropped in the epilogue
-  const uint4* wsrc[AL];
-#pragma unroll
-  for (int j = 0; j < AL; ++j) {
-    const int idx = tid + 512 * j;
-    wsrc[j] = Wt + (size_t)min(nb0 + (idx >> 6), NB - 1) * KT * 64 + (idx & 63);
-  }
-  const uint4* xsrc[CPW];
-#pragma unroll
-  for (int c = 0; c < CPW; ++c) xsrc[c] = Xs + (size_t)min(cb0 + c, CB - 1) * KT * 128 + lane;
-  uint4 ar[AL], bh[CPW], bl[CPW], bhn[CPW], bln[CPW];
-#pragma unroll
-  for (int j = 0; j < AL; ++j) ar[j] = wsrc[j][0];
-#pragma unroll
-  for (int c = 0; c < CPW; ++c) { bh[c] = xsrc[c][0]; bl[c] = xsrc[c][64]; }
-#pragma unroll
-  for (int j = 0; j < AL; ++j) as[tid + 512 * j] = ar[j];
-  __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    const int cur = kt & 1, nx = min(kt + 1, KT - 1);
-#pragma unroll
-    for (int j = 0; j < AL; ++j) ar[j] = wsrc[j][(size_t)nx * 64];
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) { bhn[c] = xsrc[c][(size_t)nx * 128]; bln[c] = xsrc[c][(size_t)nx * 128 + 64]; }
-    const uint4* ap = as + cur * (RBW * 64) + lane;
-#pragma unroll
-    for (int r = 0; r < RBW; ++r) {
-      const bf16x8 av = __builtin_bit_cast(bf16x8, ap[r * 64]);
-#pragma unroll
-      for (int c = 0; c < CPW; ++c) {
-        acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bh[c]), acc[r][c], 0, 0, 0);
-        acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bl[c]), acc[r][c], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < AL; ++j) as[(cur ^ 1) * (RBW * 64) + tid + 512 * j] = ar[j];
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) { bh[c] = bhn[c]; bl[c] = bln[c]; }
-    __syncthreads();
-  }
-  // epilogue: lane holds rows 4g+j of a row block for token lane%16 of a block of token rows; each
-  // wave works on an LDS patch of its own, so no barrier is needed below
-  float (*fin)[16] = reinterpret_cast<float (*)[16]>(reinterpret_cast<float*>(as) + wave * 256);
-  const int g = lane >> 4, token = lane & 15;
-#pragma unroll
-  for (int c = 0; c < CPW; ++c) {
-    if (cb0 + c >= CB) break;
-    const int rowbase = (cb0 + c) * 16;
-    const int mvalid = min(16, p.M - rowbase);
-    const float sc = (p.rowscale && token < mvalid) ? p.rowscale[rowbase + token] : 1.0f;
-    uint16_t* xs_out = p.XsOut ? p.XsOut + (size_t)(cb0 + c) * p.xs_out_cb_stride : nullptr;
-    float* ssq_out = p.ssq_out ? p.ssq_out + (size_t)rowbase * p.NB : nullptr;
-#pragma unroll
-    for (int r = 0; r < RBW; ++r) {
-      const int nb = nb0 + r;
-      if (nb < NB) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) fin[token][4 * g + j] = acc[r][c][j] * sc;
-        __builtin_amdgcn_wave_barrier();
-        epilogue<EPI, true, true>(p, nb, fin, mvalid, rowbase, xs_out, ssq_out);
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-  }
-}
-
-// One wave per token row: the RMS scale from the per-block sums of squares a RESID epilogue left.
-__global__ void __launch_bounds__(256) rowscale_k(const float* ssq, int nb, int M, int K, float eps, float* rowscale) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (row >= M) return;
-  float q = 0.f;
-  for (int b = lane; b < nb; b += 64) q += ssq[(size_t)row * nb + b];
-  for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
-  if (lane == 0) rowscale[row] = 1.0f / sqrtf(q / (float)K + eps);
-}
-
-// The same wide GEMM with the loads four k tiles deep.  In the form above every k tile waits for a memory
-// latency: the weight tile is stored to LDS, and the activation registers are copied from a "next" set, inside
-// the iteration that requested them.  Here both sit in rings of 4 register sets that are never copied (a copy of
-// a register that a load is still filling waits for every load in flight): iteration kt requests tile kt + 3,
-// multiplies tile kt and passes the weight tile of kt + 1, requested two iterations earlier, on to LDS (two
-// stages).  Needs KT % 4 == 0 (the rings are unrolled) and RBW == 8 (one 16-byte piece of the weight tiles per thread).
-template <int EPI, int RBW, int CPW>
-__global__ void __launch_bounds__(512) gemm_wide4_k(GemmP p, int NS, int NCG) {
-  static_assert(RBW == 8, "one piece of the weight tiles per thread and stage");
-  constexpr int CBW = 8 * CPW;
-  __shared__ __align__(16) uint4 as0[RBW * 64];   // reused by the epilogue ([8 waves][256] floats)
-  __shared__ __align__(16) uint4 as1[RBW * 64];
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-  const int cg = local % NCG, slab = (local / NCG) * 8 + xcd;
-  if (slab >= NS) return;
-  const int NB = p.NB, KT = p.KT;
-  const int CB = (p.M + 15) >> 4;
-  const int nb0 = slab * RBW, cb0 = cg * CBW + wave * CPW;
-  const uint4* Wt = (const uint4*)p.Wt;
-  const uint4* Xs = (const uint4*)p.Xs;
-  floatx4 acc[RBW][CPW];
-#pragma unroll
-  for (int r = 0; r < RBW; ++r)
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) acc[r][c] = (floatx4){0.f, 0.f, 0.f, 0.f};
-  // addresses are clamped (row blocks past the matrix, token-row blocks past the pass, k tiles past the end):
-  // no branches around memory operations; such results are dropped or never used
-  const size_t wrow = (size_t)min(nb0 + wave, NB - 1) * KT * 64;   // scalar: this wave stages row block nb0 + wave
-  size_t xrow[CPW];
-#pragma unroll
-  for (int c = 0; c < CPW; ++c) xrow[c] = (size_t)min(cb0 + c, CB - 1) * KT * 128;
-  // four register sets, named (not indexed) so that every access is to a fixed register
-  uint4 ar0, ar1, ar2, ar3, bh0[CPW], bh1[CPW], bh2[CPW], bh3[CPW], bl0[CPW], bl1[CPW], bl2[CPW], bl3[CPW];
-  auto request = [&](int kt, uint4& a, uint4* h, uint4* l) {
-    const int k = min(kt, KT - 1);
-    a = Wt[wrow + (size_t)k * 64 + lane];
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) {
-      h[c] = Xs[xrow[c] + (size_t)k * 128 + lane];
-      l[c] = Xs[xrow[c] + (size_t)k * 128 + 64 + lane];
-    }
-  };
-  auto multiply = [&](const uint4* stage, const uint4* h, const uint4* l) {
-    const uint4* ap = stage + lane;
-#pragma unroll
-    for (int r = 0; r < RBW; ++r) {
-      const bf16x8 av = __builtin_bit_cast(bf16x8, ap[r * 64]);
-#pragma unroll
-      for (int c = 0; c < CPW; ++c) {
-        acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, h[c]), acc[r][c], 0, 0, 0);
-        acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, l[c]), acc[r][c], 0, 0, 0);
-      }
-    }
-  };
-  request(0, ar0, bh0, bl0);
-  request(1, ar1, bh1, bl1);
-  request(2, ar2, bh2, bl2);
-  as0[tid] = ar0;
-  __syncthreads();
-  // (the fences keep the requests at the top of an iteration: left alone, the scheduler sinks them below the
-  // matrix instructions, next to their first use, and the ring then hides nothing)
-  for (int kt = 0; kt < KT; kt += 4) {
-    request(kt + 3, ar3, bh3, bl3);
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(as0, bh0, bl0);
-    as1[tid] = ar1;
-    __syncthreads();
-    request(kt + 4, ar0, bh0, bl0);
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(as1, bh1, bl1);
-    as0[tid] = ar2;
-    __syncthreads();
-    request(kt + 5, ar1, bh1, bl1);
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(as0, bh2, bl2);
-    as1[tid] = ar3;
-    __syncthreads();
-    request(kt + 6, ar2, bh2, bl2);
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(as1, bh3, bl3);
-    as0[tid] = ar0;
-    __syncthreads();
-  }
-  // epilogue: lane holds rows 4g+j of a row block for token lane%16 of a block of token rows; each
-  // wave works on an LDS patch of its own, so no barrier is needed below
-  float (*fin)[16] = reinterpret_cast<float (*)[16]>(reinterpret_cast<float*>(as0) + wave * 256);
-  const int g = lane >> 4, token = lane & 15;
-#pragma unroll
-  for (int c = 0; c < CPW; ++c) {
-    if (cb0 + c >= CB) break;
-    const int rowbase = (cb0 + c) * 16;
-    const int mvalid = min(16, p.M - rowbase);
-    const float sc = (p.rowscale && token < mvalid) ? p.rowscale[rowbase + token] : 1.0f;
-    uint16_t* xs_out = p.XsOut ? p.XsOut + (size_t)(cb0 + c) * p.xs_out_cb_stride : nullptr;
-    float* ssq_out = p.ssq_out ? p.ssq_out + (size_t)rowbase * p.NB : nullptr;
-#pragma unroll
-    for (int r = 0; r < RBW; ++r) {
-      const int nb = nb0 + r;
-      if (nb < NB) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) fin[token][4 * g + j] = acc[r][c][j] * sc;
-        __builtin_amdgcn_wave_barrier();
-        epilogue<EPI, true, true>(p, nb, fin, mvalid, rowbase, xs_out, ssq_out);
-        __builtin_amdgcn_wave_barrier();
       }
     }
   }
@@ -2525,60 +2291,6 @@ hipError_t launch_gemm_mfma(const GemmP& p, int epi, int waves, int col_blocks, 
       break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-namespace {
-template <int EPI, int RBW, int CPW>
-hipError_t launch_wide_inst(const GemmP& p, hipStream_t s) {
-  const int CB = (p.M + 15) / 16, NS = (p.NB + RBW - 1) / RBW, NCG = (CB + 8 * CPW - 1) / (8 * CPW);
-  dim3 grid((NS + 7) / 8 * 8 * NCG), block(512);
-  const bool deep = p.wide_form != 1;
-  // loads four k tiles deep (static LDS) where an iteration is short against a memory latency: one block of token
-  // rows per wave.  With two blocks per wave the iteration is twice as long, two work-groups per CU already hide
-  // the latency, and the rings' registers would leave room for one work-group only (measured: 330 -> 348 us on
-  // gate/up, 214 -> 244 us on QKV, against 219 -> 123 us on the output and down projections).
-  if (deep && CPW == 1 && p.KT % 4 == 0) {
-    if (p.ev_start && p.ev_stop)
-      hipExtLaunchKernelGGL((gemm_wide4_k<EPI, RBW, CPW>), grid, block, 0, s, p.ev_start, p.ev_stop, 0, p, NS, NCG);
-    else
-      hipLaunchKernelGGL((gemm_wide4_k<EPI, RBW, CPW>), grid, block, 0, s, p, NS, NCG);
-    return hipGetLastError();
-  }
-  const size_t lds = (size_t)2 * RBW * 64 * sizeof(uint4);
-  static bool raised = false;
-  if (!raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_wide_k<EPI, RBW, CPW>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    raised = true;
-  }
-  if (p.ev_start && p.ev_stop)
-    hipExtLaunchKernelGGL((gemm_wide_k<EPI, RBW, CPW>), grid, block, (uint32_t)lds, s, p.ev_start, p.ev_stop, 0, p, NS,
-                          NCG);
-  else
-    hipLaunchKernelGGL((gemm_wide_k<EPI, RBW, CPW>), grid, block, lds, s, p, NS, NCG);
-  return hipGetLastError();
-}
-}  // namespace
-
-hipError_t launch_gemm_wide(const GemmP& p, int epi, hipStream_t s) {
-  if (p.NB <= 0 || p.KT <= 0 || p.M < 1 || p.wdtype != 1 || !p.Xs) return hipErrorInvalidValue;
-  // a work-group's tile: 8 row blocks x 256 token rows; x 128 for the matrices with few rows (output and
-  // down projection), which doubles their work-groups.  (16 row blocks x 256 rows halves the activation
-  // traffic but leaves one work-group per CU and measured slower.)
-  const bool small = p.NB < 512;
-  switch (epi) {
-    case EPI_RESID: return small ? launch_wide_inst<EPI_RESID, 8, 1>(p, s) : launch_wide_inst<EPI_RESID, 8, 2>(p, s);
-    case EPI_QKV: return small ? launch_wide_inst<EPI_QKV, 8, 1>(p, s) : launch_wide_inst<EPI_QKV, 8, 2>(p, s);
-    case EPI_SWIGLU: return small ? launch_wide_inst<EPI_SWIGLU, 8, 1>(p, s) : launch_wide_inst<EPI_SWIGLU, 8, 2>(p, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-hipError_t launch_rowscale(const float* ssq, int nb, int M, int K, float eps, float* rowscale, hipStream_t s) {
-  if (M < 1 || nb < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(rowscale_k, dim3((M + 3) / 4), dim3(256), 0, s, ssq, nb, M, K, eps, rowscale);
   return hipGetLastError();
 }
 
