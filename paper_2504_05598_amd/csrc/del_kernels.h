@@ -139,8 +139,8 @@ hipError_t launch_attention(const AttnP& p, hipStream_t s);
 // the launcher rounds it down to what the shape's instantiation offers.
 hipError_t launch_attention_decode(const AttnP& p, int S, hipStream_t s, int rows_per_wg = 1);
 hipError_t launch_attention_merge(const AttnP& p, hipStream_t s);
-// Causal attention of p.m token rows on the matrix cores (bf16 caches, head_dim 64 or 128); writes O and
-// XsOut directly (no partials).  Needs VcT.
+// Causal attention of p.m token rows on the matrix cores (del_flash.hip; bf16 caches, head_dim 64 or 128); writes
+// XsOut only (no partials, no fp32 rows).  Needs VcT.
 hipError_t launch_attention_flash(const AttnP& p, hipStream_t s);
 // The same for m <= 16 token rows (verify), split over the context into S spans of at least rps_min cache rows
 // (a multiple of 32): one partial per (row, head, split) in PM / PL / PA, to be merged by launch_attention_merge.

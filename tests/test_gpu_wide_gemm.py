@@ -33,3 +33,25 @@ def test_every_prompt_length_gives_the_rows_of_the_short_passes(name, form, monk
                 assert np.linalg.norm(a - b) <= 1e-3 * np.linalg.norm(b), (name, form, plen, l, i)
     wide.close()
     short.close()
+
+
+@pytest.mark.parametrize("rows,plen", [(32, 131), (48, 203), (144, 431), (1024, 300)])
+@pytest.mark.parametrize("name", ["mini_gqa", "mini_mha", "mini_g8"])
+def test_prompt_attention_on_a_filled_cache(name, rows, plen, monkeypatch):
+    """Passes of `rows` token rows that start at cache lengths off the 64-row stages and 128-row blocks of the prompt
+    attention, one, four and eight query heads per kv head, head widths 64 and 128."""
+    from gpu_harness import gpu_context
+    cfg = get_config(name)
+    monkeypatch.setenv("DEL_PREFILL_ROWS", str(rows))
+    wide, _ = gpu_context(cfg, max_context=plen + 2)
+    monkeypatch.setenv("DEL_PREFILL_ROWS", "0")
+    short, _ = gpu_context(cfg, max_context=plen + 2)
+    prompt = gen_prompt(cfg, length=plen).tolist()
+    wide.prefill(prompt)
+    short.prefill(prompt)
+    for l in range(1, cfg.n_layers + 1):
+        for i in range(short.last_rows()):
+            a, b = wide.hidden(l, wide.last_rows() - 1 - i), short.hidden(l, short.last_rows() - 1 - i)
+            assert np.linalg.norm(a - b) <= 1e-3 * np.linalg.norm(b), (name, rows, plen, l, i)   # as above
+    wide.close()
+    short.close()
