@@ -443,8 +443,8 @@ class DelContext:
                           else f"gemm_wide_k<{e.epilogue}>" if e.flavour == 3
                           else self._rows_name(e) if e.flavour == 4
                           else f"gemm_mfma_rows_k<{e.epilogue}>" if e.flavour == 5
-                          else "head_gemm4_k" if e.flavour == 6 else "head_gemm_k")
-                out.append({"kernel": kernel, "flavour": ("valu", "mfma", "mfma", "mfma", "valu", "mfma", "mfma")[e.flavour],
+                          else "gemm_wide_k<4>")
+                out.append({"kernel": kernel, "flavour": ("valu", "mfma", "mfma", "mfma", "valu", "mfma")[e.flavour],
                             "epilogue": names[e.epilogue], "rows": e.rows, "launches": e.launches,
                             "total_ms": e.total_ms, "avg_us": 1e3 * e.total_ms / e.launches,
                             "weight_bytes": e.weight_bytes})

@@ -127,6 +127,8 @@ struct del_ctx {
   unsigned note_seq = 0;
   int* state = nullptr; int* draft_ids = nullptr; int* shadow_ids = nullptr; int* result = nullptr;
   int* ids_dev = nullptr; int* result_host = nullptr;
+  // statistics of a prompt: rows per shadow-head call, ids then confidences of L * seed_rows rows, pinned mirror
+  int seed_rows = 0; int* seed_ids = nullptr; int* seed_host = nullptr;
   size_t res_ints = 0, res_words = 0;   // ints of a round's result block / all its 32-bit words (ints, then confidences)
   float* logits_dbg = nullptr; float* sink = nullptr;
   // speculative sampling: logits and fixed-point weights of the draft rows [0, d_max] and of the
@@ -149,7 +151,6 @@ struct del_ctx {
   int target_waves = 3072;
   int rows_form = 0;          // one-row GEMV: 1 = one row block per work-group for every matrix (DEL_ROWS_FORM)
   int wide_form = 0;          // prefill GEMMs: 1 = no k range is split over work-groups (DEL_WIDE_FORM)
-  int head_form = 4;          // shadow-head kernel: 4 = register-blocked, 1 = one row block per wave (DEL_HEAD_FORM)
   // Optional (DEL_GRAPHS=1): the segments of a round are captured once per (kind, E, gamma) into HIP
   // graphs and replayed; positions and token ids live in device memory, so a graph depends on
   // nothing else.  Off by default: on this GPU the kernels of a round already run back to back
@@ -552,9 +553,9 @@ del_status head_one(del_ctx* ctx, int layer, int row, int* out_id, float* out_co
   return DEL_OK;
 }
 
-// Shadow tokens (Section 4.2): final norm + LM head + arg-max of rows 0..m-1 of every layer
-// 1..L, into shadow_ids[(l-1)*m + i], and their confidences into conf_dev[(l-1)*m + i].
-del_status shadow_head(del_ctx* ctx, int m, int row0 = 0) {
+// Shadow tokens (Section 4.2): final norm + LM head + arg-max of rows row0..row0+m-1 of every layer
+// 1..L, into ids[(l-1)*m + i], and their confidences into conf[(l-1)*m + i].
+del_status shadow_head(del_ctx* ctx, int m, int row0, int* ids, float* conf) {
   const int R = ctx->L * m;
   const bool mf = ctx->cfg.use_mfma && ctx->wd == DEL_DTYPE_BF16;
   int nparts = ctx->NBv;
@@ -562,12 +563,11 @@ del_status shadow_head(del_ctx* ctx, int m, int row0 = 0) {
     HIPCHK(launch_prep_split(ctx->hid_row(1, row0), R, m, (int64_t)ctx->hrows * ctx->dpad, ctx->dpad, ctx->d,
                              ctx->KTd, ctx->gain_final(), 1, ctx->cfg.rms_eps, ctx->xs_shadow, ctx->rowscale,
                              ctx->stream));
-    // the head is streamed once per group of column blocks: 8 blocks of 16 rows in the register-blocked form, 16 otherwise
-    const int cbs = (R + 15) / 16, per_pass = (ctx->head_form == 4 && ctx->KTd % 4 == 0) ? 8 : 16;
-    const int pr = prof_begin(ctx, per_pass == 8 ? 6 : 2, EPI_ARGMAX, R, (int64_t)((cbs + per_pass - 1) / per_pass) * ctx->NBv * ctx->KTd * 1024);
-    HIPCHK(launch_head_gemm(ctx->head_t, ctx->NBv, ctx->KTd, ctx->V, ctx->xs_shadow, R, ctx->rowscale, ctx->pval,
-                            ctx->pidx, ctx->psum, &nparts, ctx->stream, pr >= 0 ? ctx->prof_ev[2 * pr] : nullptr,
-                            pr >= 0 ? ctx->prof_ev[2 * pr + 1] : nullptr, ctx->head_form));
+    GemmP p = head_gemm(ctx);
+    p.Xs = ctx->xs_shadow; p.rowscale = ctx->rowscale; p.M = R;
+    const int pr = prof_begin(ctx, 2, EPI_ARGMAX, R, (int64_t)ctx->NBv * ctx->KTd * 1024);
+    if (pr >= 0) { p.ev_start = ctx->prof_ev[2 * pr]; p.ev_stop = ctx->prof_ev[2 * pr + 1]; }
+    HIPCHK(launch_gemm_wide_argmax(p, &nparts, ctx->stream));
     prof_end(ctx, pr);
   } else {
     for (int l = 1; l <= ctx->L; ++l) {
@@ -578,7 +578,7 @@ del_status shadow_head(del_ctx* ctx, int m, int row0 = 0) {
       if (st != DEL_OK) return st;
     }
   }
-  HIPCHK(launch_argmax_finish(ctx->pval, ctx->pidx, ctx->psum, R, nparts, ctx->shadow_ids, ctx->conf_dev, ctx->stream));
+  HIPCHK(launch_argmax_finish(ctx->pval, ctx->pidx, ctx->psum, R, nparts, ids, conf, ctx->stream));
   return DEL_OK;
 }
 
@@ -587,11 +587,12 @@ void free_all(del_ctx* c) {
                   c->rope, c->hid, c->q, c->attn, c->act, c->xs_layer, c->xs_shadow, c->rowscale, c->xs_h, c->xs_attn,
                   c->xs_h1, c->xs_act, c->ssq_h, c->ssq_h1, c->PM, c->PL,
                   c->PA, c->pval, c->pidx, c->psum, c->state, c->draft_ids, c->shadow_ids, c->result, c->ids_dev,
-                  c->logits_dbg, c->sink, c->stage, c->slog, c->swf, c->srows, c->unif_dev, c->rowscale_w, c->vct, c->wide_part};
+                  c->logits_dbg, c->sink, c->stage, c->slog, c->swf, c->srows, c->unif_dev, c->rowscale_w, c->vct, c->wide_part, c->seed_ids};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->result_host) (void)hipHostFree(c->result_host);   // conf_host and conf_dev point into the result blocks
   if (c->step_host) (void)hipHostFree(c->step_host);
+  if (c->seed_host) (void)hipHostFree(c->seed_host);
   for (auto& e : c->ev)
     if (e) (void)hipEventDestroy(e);
   for (auto& e : c->prof_ev)
@@ -699,11 +700,6 @@ del_status del_create(const del_config* cfg, void* hip_stream, del_ctx** out) {
   }
   if (const char* wf = getenv("DEL_WIDE_FORM")) ctx->wide_form = atoi(wf) == 1 ? 1 : 0;
   if (const char* rf = getenv("DEL_ROWS_FORM")) ctx->rows_form = atoi(rf) == 1 ? 1 : 0;
-  if (const char* hf = getenv("DEL_HEAD_FORM")) {
-    const int v = atoi(hf);
-    if (v == 1 || v == 4) ctx->head_form = v;
-  }
-
   const size_t tile = 1024;
   auto al = [](size_t x) { return (x + 4095) & ~(size_t)4095; };
   ctx->off_qkv = 0;
@@ -836,18 +832,24 @@ del_status del_create(const del_config* cfg, void* hip_stream, del_ctx** out) {
       CK(hipMemsetAsync(ctx->vct, 0, ctx->vct_layer_bytes * ctx->L, ctx->stream));
     }
   }
-  const size_t xs_sh = (size_t)ceil_div(Rmax, 16) * ctx->KTd * 2048;
+  // rows of a prompt's statistics window go through the shadow head in groups of up to 32: one pass over the head for the
+  // whole window of the paper (32 positions) where a wide pass holds it
+  ctx->seed_rows = ctx->prows >= 32 ? std::max(16, std::min(32, cfg->prefill_window)) : 16;
+  const int Rall = ctx->L * std::max(ctx->maxrows, ctx->seed_rows);
+  CK(dmalloc(&ctx->seed_ids, (size_t)2 * ctx->L * ctx->seed_rows * 4));
+  CK(hipHostMalloc((void**)&ctx->seed_host, (size_t)2 * ctx->L * ctx->seed_rows * 4, hipHostMallocDefault));
+  const size_t xs_sh = (size_t)ceil_div(Rall, 16) * ctx->KTd * 2048;
   CK(dmalloc(&ctx->xs_shadow, xs_sh));
   CK(hipMemsetAsync(ctx->xs_shadow, 0, xs_sh, ctx->stream));
-  CK(dmalloc(&ctx->rowscale, (size_t)(Rmax + 16) * 4));
+  CK(dmalloc(&ctx->rowscale, (size_t)(Rall + 16) * 4));
   // attention partials: [row][head][nch_max] for the short passes, [row][head][WIDE_S] for the wide ones
   const size_t prow = std::max((size_t)ctx->maxrows * ctx->nq * ctx->nch_max, (size_t)ctx->hrows * ctx->nq * WIDE_S);
   CK(dmalloc(&ctx->PM, prow * 4));
   CK(dmalloc(&ctx->PL, prow * 4));
   CK(dmalloc(&ctx->PA, prow * ctx->hd * 4));
-  CK(dmalloc(&ctx->pval, (size_t)Rmax * ctx->NBv * 4));
-  CK(dmalloc(&ctx->pidx, (size_t)Rmax * ctx->NBv * 4));
-  CK(dmalloc(&ctx->psum, (size_t)Rmax * ctx->NBv * 4));
+  CK(dmalloc(&ctx->pval, (size_t)Rall * ctx->NBv * 4));
+  CK(dmalloc(&ctx->pidx, (size_t)Rall * ctx->NBv * 4));
+  CK(dmalloc(&ctx->psum, (size_t)Rall * ctx->NBv * 4));
   CK(hipHostMalloc((void**)&ctx->step_host, 16, hipHostMallocDefault));
   memset(ctx->step_host, 0, 16);
   CK(dmalloc(&ctx->state, 16));
@@ -987,20 +989,19 @@ del_status del_prefill(del_ctx* ctx, const int32_t* prompt, int32_t n_prompt, in
       del_status st = widep ? run_layer_wide(ctx, l, mc, l > 1) : run_layer(ctx, l, 0, mc, l > 1);
       if (st != DEL_OK) return st;
     }
-    // rows of this pass inside the statistics window, in groups of up to 16
-    for (int r0 = std::max(0, P - w - start); r0 < mc; r0 += 16) {
-      const int cnt = std::min(16, mc - r0);
-      del_status st = shadow_head(ctx, cnt, r0);
+    // rows of this pass inside the statistics window, in groups
+    for (int r0 = std::max(0, P - w - start); r0 < mc; r0 += ctx->seed_rows) {
+      const int cnt = std::min(ctx->seed_rows, mc - r0);
+      del_status st = shadow_head(ctx, cnt, r0, ctx->seed_ids, reinterpret_cast<float*>(ctx->seed_ids + (size_t)L * cnt));
       if (st != DEL_OK) return st;
-      HIPCHK(hipMemcpyAsync(ctx->result_host, ctx->shadow_ids, (size_t)L * cnt * 4, hipMemcpyDeviceToHost,
-                            ctx->stream));
-      HIPCHK(hipMemcpyAsync(ctx->conf_host, ctx->conf_dev, (size_t)L * cnt * 4, hipMemcpyDeviceToHost, ctx->stream));
+      HIPCHK(hipMemcpyAsync(ctx->seed_host, ctx->seed_ids, (size_t)2 * L * cnt * 4, hipMemcpyDeviceToHost, ctx->stream));
       HIPCHK(hipStreamSynchronize(ctx->stream));
+      const float* seed_conf = reinterpret_cast<const float*>(ctx->seed_host + (size_t)L * cnt);
       for (int i = 0; i < cnt; ++i) {
         const int wpos = start + r0 + i - (P - w);
         for (int l = 1; l <= L; ++l) {
-          shadow[(size_t)(l - 1) * w + wpos] = ctx->result_host[(l - 1) * cnt + i];
-          sconf[(size_t)(l - 1) * w + wpos] = ctx->conf_host[(l - 1) * cnt + i];
+          shadow[(size_t)(l - 1) * w + wpos] = ctx->seed_host[(l - 1) * cnt + i];
+          sconf[(size_t)(l - 1) * w + wpos] = seed_conf[(l - 1) * cnt + i];
         }
       }
     }
@@ -1194,7 +1195,7 @@ static del_status round_impl(del_ctx* ctx, int E, int gamma, double tau, int32_t
   //      results to pinned host memory
   {
     del_status st = run_segment(ctx, SEG_SHADOW, E, gamma, [&]() -> del_status {
-      del_status st2 = shadow_head(ctx, m);
+      del_status st2 = shadow_head(ctx, m, 0, ctx->shadow_ids, ctx->conf_dev);
       if (st2 != DEL_OK) return st2;
       HIPCHK(launch_accept(ctx->state, ctx->draft_ids, ctx->shadow_ids, L, m, E, gamma, ctx->result, s));
       HIPCHK(hipMemcpyAsync(ctx->result_host, ctx->result, ctx->res_words * 4, hipMemcpyDeviceToHost, s));   // ids + confidences
@@ -1310,7 +1311,7 @@ static del_status round_sample_impl(del_ctx* ctx, int E, int gamma, double tau, 
   HIPCHK(hipEventRecord(ctx->ev[2], s));
   // ---- greedy shadow tokens of every layer; the target's distributions; acceptance on the device
   {
-    del_status st = shadow_head(ctx, m);
+    del_status st = shadow_head(ctx, m, 0, ctx->shadow_ids, ctx->conf_dev);
     if (st != DEL_OK) return st;
     st = sample_logits(ctx, L, 0, m, VB);
     if (st != DEL_OK) return st;

@@ -113,16 +113,11 @@ hipError_t launch_gemm_valu(const GemmP& p, int epi, int waves, hipStream_t s);
 bool gemv_rows_applies(const GemmP& p);
 bool gemm_mfma_rows_applies(const GemmP& p, int epi, int col_blocks);
 hipError_t launch_gemm_mfma(const GemmP& p, int epi, int waves, int col_blocks, hipStream_t s);
-// Shadow-head GEMM with fused arg-max over R rows; partials are [R][*n_slabs].  form 4: the register-blocked
-// kernel (needs KT % 4 == 0, otherwise the other one runs); any other value: one row block per wave.
-hipError_t launch_head_gemm(const void* Wt, int NB, int KT, int N, const uint16_t* Xs, int R, const float* rowscale,
-                            float* pval, int* pidx, float* psum, int* n_slabs, hipStream_t s,
-                            hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, int form = 1);
 // ---- GEMMs over many token rows (del_wide.hip): activations as split tiles [cb][kt] for p.M rows ----
-// How a launch is cut up: tiles of 16 row blocks x CBT blocks of 16 token rows, NCG of them side by side per slab of the
+// How a launch is cut up: tiles of 2 RW row blocks x CBT blocks of 16 token rows, NCG of them side by side per slab of the
 // matrix; the first `full` tiles run over all k, the other `rem` are split into S ranges of k.
 struct WidePlan {
-  int CBT, NCG, full, rem, S;
+  int RW, CBT, NCG, full, rem, S;
 };
 WidePlan wide_plan(int NB, int KT, int M, int whole);   // whole = 1: no splits
 size_t wide_part_bytes(const WidePlan& w);              // workspace a launch with this plan needs (p.part)
@@ -131,6 +126,9 @@ size_t wide_part_bytes(const WidePlan& w);              // workspace a launch wi
 hipError_t launch_gemm_wide(const GemmP& p, int epi, hipStream_t s);                      // with wide_plan's plan
 hipError_t launch_gemm_wide(const GemmP& p, int epi, const WidePlan& w, hipStream_t s);
 int wide_ssq_nb(int NB);
+// Shadow-head GEMM: arg-max and soft-max sums over the matrix rows, for p.M token rows; leaves *n_parts partials per row
+// (at most ceil(NB / 4)) in p.pval / p.pidx / p.psum.
+hipError_t launch_gemm_wide_argmax(const GemmP& p, int* n_parts, hipStream_t s);
 hipError_t launch_prep_split(const float* src, int rows, int rows_per_group, int64_t group_stride,
                              int ld, int K, int KT, const float* gain, int rms, float eps,
                              uint16_t* Xs, float* rowscale, hipStream_t s);

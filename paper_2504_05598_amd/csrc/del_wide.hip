@@ -1,5 +1,5 @@
-// GEMMs over many token rows (prompts, and verification of more than 16 rows): bf16 weights times activations split
-// into bf16 high + low parts, fp32 accumulation, with the layers' epilogues fused.
+// GEMMs over many token rows (prompts, verification of more than 16 rows, the shadow head over every layer's rows):
+// bf16 weights times activations split into bf16 high + low parts, fp32 accumulation, with the epilogues fused.
 #include "del_device.h"
 #include <hip/hip_ext.h>
 
@@ -9,7 +9,6 @@ namespace del {
 
 namespace {
 
-constexpr int WRB = 16;        // 16-row blocks of the matrix per tile
 constexpr int WQ = 4;          // row blocks whose sums of squares go out as one number
 
 // What a lane needs to know about its token row in an epilogue.
@@ -164,6 +163,46 @@ __device__ __forceinline__ RowCtx row_ctx(const GemmP& p, int cb, int lane) {
   return r;
 }
 
+// Best logit, its lowest index and the soft-max sum relative to it over the 16 * RW matrix rows a wave holds of one token
+// row, as partial nb0 / RW of that row.  The positive RMS scale cannot change the arg-max; it is applied because the
+// stored maximum and the sums are in logit units.
+template <int RW, int CBW>
+__device__ __forceinline__ void argmax_group(const GemmP& p, const floatx4 (&acc)[RW][CBW], int c, int nb0, int row, int g) {
+  const float sc = row < p.M && p.rowscale ? p.rowscale[row] : 1.0f;
+  float best = -INFINITY;
+  int bi = 0x7FFFFFFF;
+#pragma unroll
+  for (int r = 0; r < RW; ++r)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n = (nb0 + r) * 16 + 4 * g + j;
+      const float v = acc[r][c][j] * sc;
+      if (n < p.N && v > best) { best = v; bi = n; }   // ascending n: strict > keeps the lowest index
+    }
+#pragma unroll
+  for (int o = 16; o < 64; o <<= 1) {
+    const float ov = __shfl_xor(best, o);
+    const int oi = __shfl_xor(bi, o);
+    if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+  }
+  float se = 0.f;
+  if (p.psum) {
+#pragma unroll
+    for (int r = 0; r < RW; ++r)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if ((nb0 + r) * 16 + 4 * g + j < p.N) se += expf(acc[r][c][j] * sc - best);
+    se += __shfl_xor(se, 16);
+    se += __shfl_xor(se, 32);
+  }
+  if (g == 0 && row < p.M) {
+    const size_t o = (size_t)row * ((p.NB + RW - 1) / RW) + nb0 / RW;
+    p.pval[o] = best;
+    p.pidx[o] = bi;
+    if (p.psum) p.psum[o] = se;
+  }
+}
+
 // Contiguous share of n units for the work-groups with index b % 8 == x (one XCD under round-robin dispatch); false: none.
 __device__ __forceinline__ bool xcd_unit(int b, int n, int& u) {
   const int x = b & 7, lo = (int)((long long)n * x / 8), hi = (int)((long long)n * (x + 1) / 8);
@@ -173,13 +212,13 @@ __device__ __forceinline__ bool xcd_unit(int b, int n, int& u) {
 
 }  // namespace
 
-// One work-group of four waves = a tile of 16 row blocks of the matrix (256 rows) x CBT blocks of 16 token rows, wave
-// (wr, wc) owning 8 row blocks x CBT / 2 token blocks of it.  Weight and activation tiles are stored in operand order,
+// One work-group of four waves = a tile of 2 RW row blocks of the matrix (256 or 128 rows) x CBT blocks of 16 token rows,
+// wave (wr, wc) owning RW row blocks x CBT / 2 token blocks of it.  Weight and activation tiles are stored in operand order,
 // so a k tile goes from memory straight into LDS (no registers) and every operand read is 1 KiB in lane order, free of
 // bank conflicts.  What limits the main loop is LDS traffic against the matrix pipes: per k tile a work-group writes
-// 16 + 2 CBT KiB and reads 4 x (8 + CBT) KiB for 4 x 16 CBT instructions, 96 B per clock of matrix work at CBT = 8
-// (measured ceiling of ds_read_b128: 119 B per clock); a 128 x 128 tile would need 144.  Two stages, two work-groups
-// per CU: while one waits at the barrier the other multiplies.
+// 2 RW + 2 CBT KiB and reads 4 x (RW + CBT) KiB for 4 RW x CBT instructions, 96 B per clock of matrix work at
+// RW = CBT = 8, 144 at RW = 4 (measured ceiling of ds_read_b128: 119 B per clock).  Two to four stages, two
+// work-groups per CU: while one waits at the barrier the other multiplies.
 // Measured in us per launch against the form before it (8 row blocks x 128 or 256 token rows, one k tile of activations
 // in registers, no splits): 7B shape at 1024 rows QKV 225 -> 176, gate/up 348 -> 298 (1.24 PFLOP/s of matrix
 // instructions), output and down together 260 -> 244; 1B shape at 93 rows QKV 36 -> 16, gate/up 73 -> 28, output and
@@ -187,12 +226,15 @@ __device__ __forceinline__ bool xcd_unit(int b, int n, int& u) {
 // the most part; a large product of the vendor library reaches 1.1 to 1.5 PFLOP/s on the same card.
 // Tiles [0, plan.full) run over all k; the others are split into plan.S ranges of k, whose partial results
 // wide_finish_k adds up in order.
-template <int EPI, int CBT>
+template <int EPI, int RW, int CBT>
 __global__ void __launch_bounds__(256, 2) gemm_wide_k(GemmP p, WidePlan w) {
+  constexpr int WRB = 2 * RW;                        // row blocks per tile
   constexpr int CBW = CBT / 2;                       // token blocks per wave
+  constexpr int WP = WRB / 4;                        // weight pieces (1 KiB) a wave stages per k tile
   constexpr int STAGE = WRB * 64 + CBT * 128;        // 16-byte pieces
   constexpr int AP = 2 * CBT / 4;                    // activation pieces (1 KiB) a wave stages per k tile
-  constexpr int NST = CBT == 8 ? 2 : CBT == 4 ? 3 : 4;   // stages: as many as leave room for two work-groups per CU
+  // stages: as many as leave room for two work-groups per CU
+  constexpr int NST = STAGE * 16 * 4 <= 81920 ? 4 : STAGE * 16 * 3 <= 81920 ? 3 : 2;
   // one array per stage: the compiler then knows that the loads filling one stage do not touch the one being read
   __shared__ __align__(16) uint4 st0[STAGE];
   __shared__ __align__(16) uint4 st1[STAGE];
@@ -220,9 +262,9 @@ __global__ void __launch_bounds__(256, 2) gemm_wide_k(GemmP p, WidePlan w) {
   typedef void __attribute__((address_space(3)))* lptr_t;
   const uint4* Wt = (const uint4*)p.Wt;
   const uint4* Xs = (const uint4*)p.Xs;
-  size_t wsrc[4], xsrc[AP];
+  size_t wsrc[WP], xsrc[AP];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) wsrc[i] = (size_t)min(nb0 + wave * 4 + i, NB - 1) * KT * 64;
+  for (int i = 0; i < WP; ++i) wsrc[i] = (size_t)min(nb0 + wave * WP + i, NB - 1) * KT * 64;
 #pragma unroll
   for (int i = 0; i < AP; ++i) {
     const int q = wave * AP + i;
@@ -230,27 +272,27 @@ __global__ void __launch_bounds__(256, 2) gemm_wide_k(GemmP p, WidePlan w) {
   }
   auto request = [&](int kt, uint4* st) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(Wt + wsrc[i] + (size_t)kt * 64 + lane), (lptr_t)(st + (wave * 4 + i) * 64), 16, 0, 0);
+    for (int i = 0; i < WP; ++i)
+      __builtin_amdgcn_global_load_lds((gptr_t)(Wt + wsrc[i] + (size_t)kt * 64 + lane), (lptr_t)(st + (wave * WP + i) * 64), 16, 0, 0);
 #pragma unroll
     for (int i = 0; i < AP; ++i)
       __builtin_amdgcn_global_load_lds((gptr_t)(Xs + xsrc[i] + (size_t)kt * 128 + lane),
                                        (lptr_t)(st + WRB * 64 + (wave * AP + i) * 64), 16, 0, 0);
   };
-  floatx4 acc[8][CBW];
+  floatx4 acc[RW][CBW];
 #pragma unroll
-  for (int r = 0; r < 8; ++r)
+  for (int r = 0; r < RW; ++r)
 #pragma unroll
     for (int c = 0; c < CBW; ++c) acc[r][c] = (floatx4){0.f, 0.f, 0.f, 0.f};
   // the operands of token block c + 1 are read from LDS under block c's matrix instructions; the next stage's loads go
   // out once the first operands have been asked for
   auto multiply = [&](const uint4* st, auto&& request) {
-    const uint4* ap = st + wr * 8 * 64 + lane;
+    const uint4* ap = st + wr * RW * 64 + lane;
     const uint4* bp = st + WRB * 64 + wc * CBW * 128 + lane;
-    uint4 a[8], bh[2], bl[2];
+    uint4 a[RW], bh[2], bl[2];
     bh[0] = bp[0];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) a[r] = ap[r * 64];
+    for (int r = 0; r < RW; ++r) a[r] = ap[r * 64];
     bl[0] = bp[64];
     __builtin_amdgcn_sched_barrier(0);
     request();
@@ -263,19 +305,19 @@ __global__ void __launch_bounds__(256, 2) gemm_wide_k(GemmP p, WidePlan w) {
         bl[nxt] = bp[(c + 1) * 128 + 64];
       }
 #pragma unroll
-      for (int r = 0; r < 8; ++r)
+      for (int r = 0; r < RW; ++r)
         acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[r]), __builtin_bit_cast(bf16x8, bh[cur]), acc[r][c], 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 8; ++r)
+      for (int r = 0; r < RW; ++r)
         acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[r]), __builtin_bit_cast(bf16x8, bl[cur]), acc[r][c], 0, 0, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);    // two LDS reads, then a block's matrix instructions
-      __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 2 * RW, 0);
     }
   };
   // one k tile: its stage has arrived for every wave once all have passed the barrier, which also says that the stage
   // of the tile before is no longer being read: it takes the tile NST - 1 further on.  Loads complete in order, so
   // leaving those of the NST - 2 younger stages in flight is enough.
-  constexpr int LEFT = (NST - 2) * (4 + AP);
+  constexpr int LEFT = (NST - 2) * (WP + AP);
   static_assert(LEFT < 16, "the wait below sets the low four bits of vmcnt only");
   auto step = [&](int kt, const uint4* cur, uint4* nxt) {
     __builtin_amdgcn_sched_barrier(0);
@@ -316,11 +358,19 @@ __global__ void __launch_bounds__(256, 2) gemm_wide_k(GemmP p, WidePlan w) {
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(0x0F70);     // no load into LDS is left in flight
   if (part >= 0) {
-    floatx4* o = (floatx4*)p.part + ((size_t)part * CBT + wc * CBW) * WRB * 64 + wr * 8 * 64 + lane;
+    floatx4* o = (floatx4*)p.part + ((size_t)part * CBT + wc * CBW) * WRB * 64 + wr * RW * 64 + lane;
 #pragma unroll
     for (int c = 0; c < CBW; ++c)
 #pragma unroll
-      for (int r = 0; r < 8; ++r) o[((size_t)c * WRB + r) * 64] = acc[r][c];
+      for (int r = 0; r < RW; ++r) o[((size_t)c * WRB + r) * 64] = acc[r][c];
+    return;
+  }
+  if (EPI == EPI_ARGMAX) {
+#pragma unroll
+    for (int c = 0; c < CBW; ++c) {
+      const int cb = cb0 + wc * CBW + c;
+      if (cb < CB && nb0 + wr * RW < NB) argmax_group<RW, CBW>(p, acc, c, nb0 + wr * RW, cb * 16 + (lane & 15), g);
+    }
     return;
   }
 #pragma unroll
@@ -330,9 +380,9 @@ __global__ void __launch_bounds__(256, 2) gemm_wide_k(GemmP p, WidePlan w) {
     RowCtx r = row_ctx<EPI>(p, cb, lane);
     if (EPI != EPI_RESID) r.sc = row_scale(p, r.valid ? r.row : 0, g);
 #pragma unroll
-    for (int q = 0; q < 8; q += WQ) {
+    for (int q = 0; q < RW; q += WQ) {
       const floatx4 v[WQ] = {acc[q][c], acc[q + 1][c], acc[q + 2][c], acc[q + 3][c]};
-      epilogue_quad<EPI>(p, nb0 + wr * 8 + q, v, r, g);
+      epilogue_quad<EPI>(p, nb0 + wr * RW + q, v, r, g);
     }
   }
 }
@@ -341,8 +391,10 @@ __global__ void __launch_bounds__(256, 2) gemm_wide_k(GemmP p, WidePlan w) {
 // one block of 16 token rows.
 template <int EPI>
 __global__ void __launch_bounds__(256) wide_finish_k(GemmP p, WidePlan w) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, quad = threadIdx.x >> 6;
-  const int c = blockIdx.x % w.CBT, r0 = blockIdx.x / w.CBT;
+  const int WRB = 2 * w.RW, quads = WRB / WQ;
+  const int lane = threadIdx.x & 63, g = lane >> 4, unit = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int quad = unit % quads, c = unit / quads % w.CBT, r0 = unit / quads / w.CBT;
+  if (r0 >= w.rem) return;
   const int tile = w.full + r0, slab = tile / w.NCG, cb = (tile - slab * w.NCG) * w.CBT + c;
   const int nb0 = slab * WRB + quad * WQ;
   if (cb * 16 >= p.M || nb0 >= p.NB) return;
@@ -362,63 +414,79 @@ __global__ void __launch_bounds__(256) wide_finish_k(GemmP p, WidePlan w) {
 }
 
 // How a launch is cut up: the cheapest plan of a small model of the kernel, whose constants are what it measured on
-// matrices of 192 to 1728 row blocks and 64 to 896 k tiles with 32 to 1024 token rows (largest error 15 %).  A k tile
-// costs a work-group ALONE_US when it has its CU to itself (a barrier and a memory latency per tile) and SHARED_US per
-// work-group when there are several (bound by what LDS and L2 deliver); the weights come in at HBM_BYTES_PER_US at
-// best.  Splitting k adds a launch and the partial results' way through the caches.
-// E.g. 256 x 11008 (7B down projection, 256 row blocks, 344 k tiles) at 1024 rows: 296 us unsplit, 171 in two, 161 in
-// four ranges; at 256 rows 156 / 86 / 54 / 55 us with 1 / 2 / 4 / 8.
+// matrices of 128 to 8016 row blocks and 64 to 896 k tiles with 8 to 1024 token rows (most plans within 15 %).  A k tile
+// costs a work-group `alone` us when it has its CU to itself (a barrier and a memory latency per tile) and `shared` us
+// per work-group when there are several (bound by what LDS and L2 deliver); the weights come in at HBM_BYTES_PER_US at
+// best.  Splitting k adds a launch, a step per part and the partial results' way through the caches.  Per wave 8 row
+// blocks read LDS least (large products); 4 give twice the tiles where those would not fill the chip.
+// E.g. 256 row blocks, 344 k tiles (7B down projection): at 1024 rows 296 us unsplit, 171 in two, 161 in four ranges;
+// at 256 rows 156 / 86 / 54 / 55 us with 1 / 2 / 4 / 8.  192 row blocks, 64 k tiles (1B QKV) at 256 rows: 20.0 us with 8
+// row blocks per wave (two ranges), 13.8 with 4 (unsplit).
 WidePlan wide_plan(int NB, int KT, int M, int whole) {
-  constexpr double ALONE_US[3] = {0.43, 0.45, 0.92}, SHARED_US[3] = {0.25, 0.47, 0.77};   // CBT = 2, 4, 8
-  constexpr double START_US = 3.0, LAUNCH_US = 4.0, HBM_BYTES_PER_US = 5.5e6, PART_BYTES_PER_US = 8.0e6;
+  struct Form { int RW, CBT; double alone, shared; };   // us per k tile
+  constexpr Form forms[] = {{8, 2, 0.41, 0.25}, {8, 4, 0.55, 0.44}, {8, 8, 0.95, 0.76},
+                            {4, 2, 0.18, 0.17}, {4, 4, 0.30, 0.27}, {4, 8, 0.56, 0.46}};
+  constexpr double START_US = 3.0, LAUNCH_US = 4.0, PER_PART_US = 0.25, HBM_BYTES_PER_US = 5.5e6, PART_BYTES_PER_US = 8.0e6;
   constexpr int CUS = 256, MAX_PART = 512, MAX_SPLIT = 32, MIN_KT = 4;
   WidePlan best{};
   double best_t = 1e30;
   const int CB = (M + 15) / 16;
-  for (int i = 0; i < 3; ++i) {
-    const int cbt = 2 << i, NCG = (CB + cbt - 1) / cbt, T = (NB + WRB - 1) / WRB * NCG;
+  for (const Form& f : forms) {
+    const int wrb = 2 * f.RW, NCG = (CB + f.CBT - 1) / f.CBT, T = (NB + wrb - 1) / wrb * NCG;
     for (int S = 1; S <= MAX_SPLIT; ++S) {
       const int full = S > 1 ? T / CUS * CUS : T, rem = T - full;
       if (S > 1 && (whole || rem == 0 || S * MIN_KT > KT || rem * S > MAX_PART)) break;
       const int wgs = (full + CUS - 1) / CUS + (rem * S + CUS - 1) / CUS;   // work-groups of the busiest CU
       const double kts = (double)((full + CUS - 1) / CUS) * KT + (double)((rem * S + CUS - 1) / CUS) * ((KT + S - 1) / S);
-      double t = std::max((wgs > 1 ? SHARED_US[i] : ALONE_US[i]) * kts, (double)NB * KT * 1024 / HBM_BYTES_PER_US);
+      double t = std::max((wgs > 1 ? f.shared : f.alone) * kts, (double)NB * KT * 1024 / HBM_BYTES_PER_US);
       t += START_US;
-      if (S > 1) t += LAUNCH_US + 2.0 * rem * S * cbt * WRB * 1024 / PART_BYTES_PER_US;
+      if (S > 1) t += LAUNCH_US + PER_PART_US * S + 2.0 * rem * S * f.CBT * wrb * 1024 / PART_BYTES_PER_US;
       if (t < best_t) {
         best_t = t;
-        best = WidePlan{cbt, NCG, full, rem, S};
+        best = WidePlan{f.RW, f.CBT, NCG, full, rem, S};
       }
     }
   }
   return best;
 }
 
-size_t wide_part_bytes(const WidePlan& w) { return (size_t)w.rem * w.S * w.CBT * WRB * 1024; }
+size_t wide_part_bytes(const WidePlan& w) { return w.rem ? (size_t)w.rem * w.S * w.CBT * 2 * w.RW * 1024 : 0; }
 int wide_ssq_nb(int NB) { return (NB + WQ - 1) / WQ; }
 
 namespace {
 
-template <int EPI, int CBT>
+template <int EPI, int RW, int CBT>
 hipError_t launch_tile(const GemmP& p, const WidePlan& w, hipStream_t s) {
   const dim3 grid((w.full + 7) / 8 * 8 + (w.rem * w.S + 7) / 8 * 8), block(256);
   const bool split = w.rem > 0;
-  hipExtLaunchKernelGGL((gemm_wide_k<EPI, CBT>), grid, block, 0, s, p.ev_start, split ? nullptr : p.ev_stop, 0, p, w);
-  if (split) hipExtLaunchKernelGGL((wide_finish_k<EPI>), dim3(w.rem * w.CBT), block, 0, s, nullptr, p.ev_stop, 0, p, w);
+  hipExtLaunchKernelGGL((gemm_wide_k<EPI, RW, CBT>), grid, block, 0, s, p.ev_start, split ? nullptr : p.ev_stop, 0, p, w);
+  if constexpr (EPI != EPI_ARGMAX)
+    if (split)
+      hipExtLaunchKernelGGL((wide_finish_k<EPI>), dim3((w.rem * w.CBT * (2 * RW / WQ) + 3) / 4), block, 0, s, nullptr,
+                            p.ev_stop, 0, p, w);
   return hipGetLastError();
 }
 
 template <int EPI>
 hipError_t launch_epi(const GemmP& p, const WidePlan& w, hipStream_t s) {
-  switch (w.CBT) {
-    case 2: return launch_tile<EPI, 2>(p, w, s);
-    case 4: return launch_tile<EPI, 4>(p, w, s);
-    case 8: return launch_tile<EPI, 8>(p, w, s);
-    default: return hipErrorInvalidValue;
-  }
+  if (w.RW == 8 && w.CBT == 8) return launch_tile<EPI, 8, 8>(p, w, s);
+  if (w.RW == 8 && w.CBT == 4) return launch_tile<EPI, 8, 4>(p, w, s);
+  if (w.RW == 8 && w.CBT == 2) return launch_tile<EPI, 8, 2>(p, w, s);
+  if (w.RW == 4 && w.CBT == 8) return launch_tile<EPI, 4, 8>(p, w, s);
+  if (w.RW == 4 && w.CBT == 4) return launch_tile<EPI, 4, 4>(p, w, s);
+  if (w.RW == 4 && w.CBT == 2) return launch_tile<EPI, 4, 2>(p, w, s);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
+
+// Shadow-head GEMM with fused arg-max over p.M rows: p.pval / pidx / psum receive *n_parts partials per row.
+hipError_t launch_gemm_wide_argmax(const GemmP& p, int* n_parts, hipStream_t s) {
+  if (p.NB <= 0 || p.KT <= 0 || p.M < 1 || !p.pval || !p.pidx) return hipErrorInvalidValue;
+  const WidePlan w = wide_plan(p.NB, p.KT, p.M, 1);
+  *n_parts = (p.NB + w.RW - 1) / w.RW;
+  return launch_gemm_wide(p, EPI_ARGMAX, w, s);
+}
 
 hipError_t launch_gemm_wide(const GemmP& p, int epi, hipStream_t s) {
   if (p.NB <= 0 || p.KT <= 0 || p.M < 1) return hipErrorInvalidValue;
@@ -432,6 +500,7 @@ hipError_t launch_gemm_wide(const GemmP& p, int epi, const WidePlan& w, hipStrea
     case EPI_RESID: return launch_epi<EPI_RESID>(p, w, s);
     case EPI_QKV: return launch_epi<EPI_QKV>(p, w, s);
     case EPI_SWIGLU: return launch_epi<EPI_SWIGLU>(p, w, s);
+    case EPI_ARGMAX: return w.rem ? hipErrorInvalidValue : launch_epi<EPI_ARGMAX>(p, w, s);
     default: return hipErrorInvalidValue;
   }
 }
