@@ -1382,52 +1382,69 @@ __global__ void __launch_bounds__(256) embed_k(const void* Et, int KT, int vocab
 // its soft-max probability 1 / sum_b psum[b] * exp(max_b - max) (Section 4.4).
 // emb_out (optional, one row): the winner's embedding row goes there as fp32 (the next draft step's input),
 // read from the tiled embedding Et (kpl = 8 bf16 or 4 fp32 elements per lane and tile).
-__global__ void __launch_bounds__(256) argmax_finish_k(const float* pval, const int* pidx, const float* psum, int NB,
-                                                       int* out_ids, float* out_conf, const void* Et, int kpl,
-                                                       int KT_e, int vocab, float* emb_out, int d_model,
-                                                       unsigned long long* note, unsigned seq) {
-  __shared__ float sv[256];
-  __shared__ int si[256];
-  const int row = blockIdx.x, tid = threadIdx.x;
-  float best = -INFINITY;
+// Bound by memory latency, one round trip per batch of loads: a thread asks for AF_UN partials of all three arrays at
+// once (one at a time, in a second pass for the sums, 8016 partials took 22 us).
+constexpr int AF_UN = 8;
+__global__ void __launch_bounds__(1024) argmax_finish_k(const float* pval, const int* pidx, const float* psum, int NB,
+                                                        int* out_ids, float* out_conf, const void* Et, int kpl,
+                                                        int KT_e, int vocab, float* emb_out, int d_model,
+                                                        unsigned long long* note, unsigned seq) {
+  __shared__ float sv[MAXW], sw[MAXW];
+  __shared__ int si[MAXW];
+  const int row = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x, wave = tid >> 6, nw = nthr >> 6;
+  const float* pv = pval + (size_t)row * NB;
+  const int* pi = pidx + (size_t)row * NB;
+  const bool conf = psum && out_conf;
+  const float* ps = conf ? psum + (size_t)row * NB : pv;   // (unused values where there is no confidence)
+  float best = -INFINITY, se = 0.f;                        // se: relative to best
   int bi = 0x7FFFFFFF;
-  for (int b = tid; b < NB; b += 256) {
-    const float v = pval[(size_t)row * NB + b];
-    const int ix = pidx[(size_t)row * NB + b];
+  for (int b0 = tid; b0 < NB; b0 += AF_UN * nthr) {
+    float v[AF_UN], w[AF_UN];
+    int ix[AF_UN];
+#pragma unroll
+    for (int u = 0; u < AF_UN; ++u) {
+      const int b = min(b0 + u * nthr, NB - 1);
+      v[u] = pv[b]; ix[u] = pi[b]; w[u] = ps[b];
+    }
+    const float before = best;
+#pragma unroll
+    for (int u = 0; u < AF_UN; ++u) {
+      if (b0 + u * nthr >= NB) v[u] = -INFINITY;
+      if (v[u] > best || (v[u] == best && ix[u] < bi && b0 + u * nthr < NB)) { best = v[u]; bi = ix[u]; }
+    }
+    if (conf) {
+      se = before > -INFINITY ? se * expf(before - best) : 0.f;
+#pragma unroll
+      for (int u = 0; u < AF_UN; ++u)
+        if (v[u] > -INFINITY) se += w[u] * expf(v[u] - best);
+    }
+  }
+  const float mine = best;
+  for (int o = 32; o > 0; o >>= 1) {
+    const float v = __shfl_xor(best, o);
+    const int ix = __shfl_xor(bi, o);
     if (v > best || (v == best && ix < bi)) { best = v; bi = ix; }
   }
-  sv[tid] = best; si[tid] = bi;
+  if ((tid & 63) == 0) { sv[wave] = best; si[wave] = bi; }
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) {
-      const float v = sv[tid + s];
-      const int ix = si[tid + s];
-      if (v > sv[tid] || (v == sv[tid] && ix < si[tid])) { sv[tid] = v; si[tid] = ix; }
-    }
-    __syncthreads();
-  }
-  const float M = sv[0];
-  const int winner = si[0];
+  float M = sv[0];
+  int winner = si[0];
+  for (int w = 1; w < nw; ++w)
+    if (sv[w] > M || (sv[w] == M && si[w] < winner)) { M = sv[w]; winner = si[w]; }
   if (tid == 0) out_ids[row] = winner;
   if (emb_out && row == 0) {
     const int id = winner < 0 ? 0 : (winner >= vocab ? vocab - 1 : winner);
-    gather_embedding(Et, kpl, KT_e, id, emb_out, d_model, tid, 256);
+    gather_embedding(Et, kpl, KT_e, id, emb_out, d_model, tid, nthr);
   }
-  if (psum && out_conf) {
+  if (conf) {
+    se = mine > -INFINITY ? se * expf(mine - M) : 0.f;
+    for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o);
+    if ((tid & 63) == 0) sw[wave] = se;
     __syncthreads();
-    float se = 0.f;
-    for (int b = tid; b < NB; b += 256) {
-      const float v = pval[(size_t)row * NB + b];
-      if (v > -INFINITY) se += psum[(size_t)row * NB + b] * expf(v - M);
-    }
-    sv[tid] = se;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (tid < s) sv[tid] += sv[tid + s];
-      __syncthreads();
-    }
     if (tid == 0) {
-      const float cf = 1.0f / sv[0];
+      float sum = 0.f;
+      for (int w = 0; w < nw; ++w) sum += sw[w];
+      const float cf = 1.0f / sum;
       out_conf[row] = cf;
       // for a host that polls pinned memory instead of waiting for the stream: sequence number and
       // confidence in one 8-byte store
@@ -1889,7 +1906,10 @@ hipError_t launch_argmax_finish(const float* pval, const int* pidx, const float*
                                 float* out_conf, hipStream_t s, const void* Et, int wdtype, int KT_e, int vocab,
                                 float* emb_out, int d_model, unsigned long long* note, unsigned seq) {
   if ((emb_out && (rows != 1 || !Et)) || (note && !(psum && out_conf))) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(argmax_finish_k, dim3(rows), dim3(256), 0, s, pval, pidx, psum, NB, out_ids, out_conf, Et,
+  // 16 waves where one row has more partials than four waves ask for at once, or a long embedding row to fetch; four
+  // otherwise (a launch of 16 waves and their longer reduction cost the 256 partials of a small vocabulary 1 us)
+  const bool big = rows == 1 && (NB > 256 * AF_UN || d_model > 4096);
+  hipLaunchKernelGGL(argmax_finish_k, dim3(rows), dim3(big ? 1024 : 256), 0, s, pval, pidx, psum, NB, out_ids, out_conf, Et,
                      wdtype == 1 ? 8 : 4, KT_e, vocab, emb_out, d_model, note, seq);
   return hipGetLastError();
 }
