@@ -117,6 +117,7 @@ struct del_ctx {
   float* ssq_h = nullptr; float* ssq_h1 = nullptr;
   float* PM = nullptr; float* PL = nullptr; float* PA = nullptr; int nch_max = 0, attn_ct = 64, attn_S = 0, attn_dec_rows = 16;
   int attn_direct_rows = 0;   // passes of at least this many rows (> 1): one context split per row, no merge kernel   // attn_S > 0: register decode kernel with S splits
+  bool attn_row = false;      // one row: attention on the matrix cores (where the feature-major values are kept)
   bool verify_flash = true;   // passes of 2..16 rows: attention on the matrix cores, split over the context
   int verify_flash_waves = 1024;   // waves (splits x query heads) that kernel aims for
   float* pval = nullptr; int* pidx = nullptr; float* psum = nullptr;
@@ -367,8 +368,17 @@ del_status run_layer(del_ctx* ctx, int l, int row0, int m, bool chained) {
   // few token rows: the register kernel, one work-group per (split, kv head, row); a single row's
   // partials are merged by the O projection itself, several rows' by the merge kernel
   const bool dec_any = ctx->attn_S > 0 && m <= ctx->attn_dec_rows;
-  const bool dec = dec_any && m == 1;
-  if (mf && VcT && ctx->verify_flash && row0 == 0) {
+  // one row with the feature-major values at hand: on the matrix cores, as many splits as the context it attends needs
+  // (under graph replay, where a launch must not depend on it: the longest)
+  const bool row_mc = m == 1 && ctx->attn_row && VcT;
+  const int n_ctx = a.ctx_len1 ? a.ctx_len1 + row0 : ctx->Tcap;
+  int dec_S = row_mc ? std::min(attention_row_splits(n_ctx), ctx->nch_max) : ctx->attn_S;
+  const bool dec = dec_any && m == 1 && !(row_mc && dec_S == 1);   // the output projection merges dec_S partials
+  if (row_mc) {
+    a.VcT = VcT; a.TcapT = ctx->TcapT;
+    if (dec_S == 1) a.nsplit = -1;
+    HIPCHK(launch_attention_row(a, dec_S, n_ctx, ctx->stream));
+  } else if (mf && VcT && ctx->verify_flash && row0 == 0) {
     // several rows (verify): on the matrix cores, the cache read once for all rows, split over the
     // context so that splits x query heads waves are in flight; then the merge
     // the split plan depends on the cache capacity only, never on the current length: a round's launch
@@ -400,7 +410,7 @@ del_status run_layer(del_ctx* ctx, int l, int row0, int m, bool chained) {
   p.R = hin; p.ldr = ctx->dpad; p.Y = hout; p.ldy = ctx->dpad;
   if (dec) {
     p.att_PM = ctx->PM; p.att_PL = ctx->PL; p.att_PA = ctx->PA;
-    p.att_S = ctx->attn_S; p.att_stride = ctx->nch_max; p.att_hd = ctx->hd;
+    p.att_S = dec_S; p.att_stride = ctx->nch_max; p.att_hd = ctx->hd;
   }
   if (mf) {
     p.Xs = ctx->xs_attn;
@@ -723,7 +733,9 @@ del_status del_create(const del_config* cfg, void* hip_stream, del_ctx** out) {
   if (attention_decode_supported(ctx->wd, ctx->hd, ctx->nq / ctx->nkv)) {
     // about 128 work-groups, at most 8 partials per head for the consumer to merge
     ctx->attn_S = std::max(1, std::min(std::min(8, ctx->nch_max), ceil_div(128, ctx->nkv)));
-    if (const char* e = getenv("DEL_ATTN_SPLITS")) {
+    ctx->attn_row = attention_row_supported(ctx->wd, ctx->hd, ctx->nq / ctx->nkv);
+    if (const char* e = getenv("DEL_ATTN_SPLITS")) {   // the vector kernel with that many splits
+      ctx->attn_row = false;
       const int v = atoi(e);
       if (v >= 0 && v <= std::min(8, ctx->nch_max)) ctx->attn_S = v;   // 0: staged kernels everywhere; 8: what the merge in the output projection takes
     }

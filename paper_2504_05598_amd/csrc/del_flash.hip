@@ -1,5 +1,7 @@
-// Causal attention of many token rows on the matrix cores (prompt passes).
+// Attention on the matrix cores: causal over many token rows (prompt passes), and of one token row (draft steps).
 #include "del_device.h"
+
+#include <algorithm>
 
 namespace del {
 
@@ -194,6 +196,165 @@ __global__ void __launch_bounds__(256, 2) attn_flash_k(AttnP p) {
       *(uint2*)(dst + 512) = lo;
     }
   }
+}
+
+// Attention of one token row: one work-group per (split of the context, kv head), NWV waves, a wave = 32 cache rows at a
+// time for all query heads of the group at once (they are the columns of the matrix-core products above; columns past
+// the group repeat its first head and are dropped).  Bound by latency: position -> cache rows -> two short products ->
+// merge of the waves through LDS.  The vector form before it (one lane group per cache row, every query head on its own:
+// a dot product, three shuffles and two exponentials per head and row, the same again to merge the lane groups) grew with
+// the heads of a group.
+template <int HD, int NWV>
+__global__ void __launch_bounds__(64 * NWV) attn_row_k(AttnP p) {
+  constexpr int KT = HD / 32, DT = HD / 16, GMAX = 16;
+  __shared__ float sm[NWV][GMAX], sl[NWV][GMAX];
+  __shared__ __align__(16) float so[NWV][GMAX][HD + 4];   // (+ 4: the 16 columns of a store fall into different banks)
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, qi = lane & 15;
+  const int split = blockIdx.x, kvh = blockIdx.y, S = gridDim.x, G = p.n_q / p.n_kv;
+  const float* qp = p.Q + (size_t)(kvh * G + (qi < G ? qi : 0)) * HD + 8 * g;
+  float4 qa[KT], qb[KT];
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt) { qa[kt] = *(const float4*)(qp + 32 * kt); qb[kt] = *(const float4*)(qp + 32 * kt + 4); }
+  const int T_end = (p.ctx_len1 ? p.ctx_len1 - 1 : p.state[0]) + p.row_off + 1;   // the row attends cache rows [0, T_end)
+  const int rps = ((T_end + S - 1) / S + 31) / 32 * 32;
+  const int t_lo = split * rps, t_hi = min(T_end, t_lo + rps);
+  const uint16_t* Kb = (const uint16_t*)p.Kc + (size_t)kvh * p.Tcap * HD + 8 * g;
+  const uint16_t* Vt = (const uint16_t*)p.VcT + ((size_t)kvh * HD + qi) * p.TcapT + 8 * g;
+  const int rho = 8 * (qi >> 2) + (qi & 3);
+  float mrun = -INFINITY, lrun = 0.f;                  // lrun: this lane's cache rows only
+  floatx4 o[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = (floatx4){0.f, 0.f, 0.f, 0.f};
+  bf16x8 qh[KT], ql[KT];
+  auto load = [&](int t0, uint4* a0, uint4* a1, uint4* av) {
+    // rows past the last one are read from it and masked in the scores
+    const uint16_t* k0 = Kb + (size_t)min(t0 + rho, T_end - 1) * HD;
+    const uint16_t* k1 = Kb + (size_t)min(t0 + rho + 4, T_end - 1) * HD;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      a0[kt] = *(const uint4*)(k0 + 32 * kt);
+      a1[kt] = *(const uint4*)(k1 + 32 * kt);
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) av[dt] = *(const uint4*)(Vt + (size_t)(16 * dt) * p.TcapT + t0);
+  };
+  auto compute = [&](int t0, const uint4* a0, const uint4* a1, const uint4* av) __attribute__((always_inline)) {
+    floatx4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      const bf16x8 x0 = __builtin_bit_cast(bf16x8, a0[kt]), x1 = __builtin_bit_cast(bf16x8, a1[kt]);
+      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, qh[kt], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, qh[kt], s1, 0, 0, 0);
+      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, ql[kt], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, ql[kt], s1, 0, 0, 0);
+    }
+    float sv[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if (t0 + 8 * g + e >= t_hi) sv[e] = -INFINITY;   // (row t0 itself is always inside)
+      mx = fmaxf(mx, sv[e]);
+    }
+    mx = fmaxf(mrun, max_of_query(mx));
+    const float c = expf(mrun - mx);                   // first tile: exp(-inf) = 0
+    mrun = mx;
+    float pv[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) pv[e] = expf(sv[e] - mx);
+    lrun = lrun * c + (((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7])));
+    bf16x8 ph, pl;
+    split8_op(pv, ph, pl);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[dt][j] *= c;
+      const bf16x8 x = __builtin_bit_cast(bf16x8, av[dt]);
+      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, ph, o[dt], 0, 0, 0);
+      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, pl, o[dt], 0, 0, 0);
+    }
+  };
+  constexpr int STEP = 32 * NWV;
+  const int first = t_lo + wave * 32;
+  if (first < t_hi) {                                  // wave-uniform
+    // two register sets used in turn, the next tile's rows requested before the current tile is multiplied
+    uint4 ka0[KT], ka1[KT], va[DT], kb0[KT], kb1[KT], vb[DT];
+    load(first, ka0, ka1, va);
+    const float scale = 1.0f / sqrtf((float)HD);
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      const float v[8] = {qa[kt].x * scale, qa[kt].y * scale, qa[kt].z * scale, qa[kt].w * scale,
+                          qb[kt].x * scale, qb[kt].y * scale, qb[kt].z * scale, qb[kt].w * scale};
+      split8_op(v, qh[kt], ql[kt]);
+    }
+    for (int t0 = first; t0 < t_hi; t0 += 2 * STEP) {
+      if (t0 + STEP < t_hi) load(t0 + STEP, kb0, kb1, vb);
+      compute(t0, ka0, ka1, va);
+      if (t0 + STEP >= t_hi) break;
+      if (t0 + 2 * STEP < t_hi) load(t0 + 2 * STEP, ka0, ka1, va);
+      compute(t0 + STEP, kb0, kb1, vb);
+    }
+  }
+  lrun += __shfl_xor(lrun, 16);
+  lrun += __shfl_xor(lrun, 32);
+  if (qi < G) {
+    if (g == 0) { sm[wave][qi] = mrun; sl[wave][qi] = lrun; }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) *(floatx4*)&so[wave][qi][16 * dt + 4 * g] = o[dt];
+  }
+  __syncthreads();
+  // the waves in a fixed order; one partial per (query head, split), or the result itself
+  for (int i = tid; i < G * HD; i += 64 * NWV) {
+    const int c = i / HD, d = i - c * HD;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) M = fmaxf(M, sm[w][c]);
+    float L = 0.f, A = 0.f;
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) {
+      const float f = sm[w][c] > -INFINITY ? expf(sm[w][c] - M) : 0.f;
+      L += f * sl[w][c];
+      A += f * so[w][c][d];
+    }
+    const int h = kvh * G + c;
+    if (S == 1 && p.nsplit < 0) {
+      p.O[(size_t)h * HD + d] = A / L;
+      continue;
+    }
+    const size_t prow = (size_t)h * p.nch_max + split;
+    if (d == 0) { p.PM[prow] = M; p.PL[prow] = L; }
+    p.PA[prow * HD + d] = A;
+  }
+}
+
+// Work-groups along the context for a row that attends n cache rows: one tile of 32 rows per wave of four waves, as many
+// partials as the output projection's staging merges at most.
+int attention_row_splits(int n) { return std::min(8, (n + 127) / 128); }
+
+// Groups of several query heads: one launch, vector form -> this one, 64 heads on 8 kv heads of width 128 at 1050 rows
+// 21.1 -> 7.2 us, 32 on 8 of width 64 at 540 rows 9.8 -> 4.9, 8 on 2 of width 64 at 70 rows 8.5 -> 3.7.  With a kv head per
+// query head 15 of 16 columns are idle and the values come in 64-byte pieces; there the vector form stays: 32 heads at
+// 1050 rows 8.1 us and 9.7 for the projection that merges its four partials, here 7.4 and 10.5 (eight partials); 40
+// heads at 2000 rows 11.4 against 14.5.
+bool attention_row_supported(int kvdtype, int hd, int G) {
+  return kvdtype == 1 && (hd == 64 || hd == 128) && G > 1 && G <= 16;
+}
+
+// p.m == 1.  S context splits; S == 1 with p.nsplit < 0 writes the output row, otherwise the partials.  Eight waves where
+// four would each see more than one tile of the longest context the splits may have.
+hipError_t launch_attention_row(const AttnP& p, int S, int n_max, hipStream_t s) {
+  if (p.m != 1 || !attention_row_supported(p.kvdtype, p.hd, p.n_q / p.n_kv) || !p.VcT || p.TcapT % 32 != 0 ||
+      p.TcapT < p.Tcap || p.n_q % p.n_kv != 0 || S < 1 || S > p.nch_max || (p.nsplit >= 0 && (!p.PM || !p.PL || !p.PA)))
+    return hipErrorInvalidValue;
+  const dim3 grid(S, p.n_kv);
+  const bool eight = (n_max + S - 1) / S > 128;
+  if (p.hd == 128) {
+    if (eight) hipLaunchKernelGGL((attn_row_k<128, 8>), grid, dim3(512), 0, s, p);
+    else hipLaunchKernelGGL((attn_row_k<128, 4>), grid, dim3(256), 0, s, p);
+  } else {
+    if (eight) hipLaunchKernelGGL((attn_row_k<64, 8>), grid, dim3(512), 0, s, p);
+    else hipLaunchKernelGGL((attn_row_k<64, 4>), grid, dim3(256), 0, s, p);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_attention_flash(const AttnP& p, hipStream_t s) {

@@ -140,6 +140,11 @@ hipError_t launch_attention_merge(const AttnP& p, hipStream_t s);
 // Causal attention of p.m token rows on the matrix cores (del_flash.hip; bf16 caches, head_dim 64 or 128); writes
 // XsOut only (no partials, no fp32 rows).  Needs VcT.
 hipError_t launch_attention_flash(const AttnP& p, hipStream_t s);
+// One token row (p.m == 1) on the matrix cores, S splits of a context of at most n_max rows: partials for the output
+// projection to merge, or (S == 1 and p.nsplit < 0) the output row.  Needs VcT.
+int attention_row_splits(int n);
+bool attention_row_supported(int kvdtype, int hd, int G);
+hipError_t launch_attention_row(const AttnP& p, int S, int n_max, hipStream_t s);
 // The same for m <= 16 token rows (verify), split over the context into S spans of at least rps_min cache rows
 // (a multiple of 32): one partial per (row, head, split) in PM / PL / PA, to be merged by launch_attention_merge.
 hipError_t launch_attention_flash_split(const AttnP& p, int S, int rps_min, hipStream_t s);
