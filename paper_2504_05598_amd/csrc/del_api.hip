@@ -128,8 +128,7 @@ struct del_ctx {
   unsigned note_seq = 0;
   int* state = nullptr; int* draft_ids = nullptr; int* shadow_ids = nullptr; int* result = nullptr;
   int* ids_dev = nullptr; int* result_host = nullptr;
-  // statistics of a prompt: rows per shadow-head call, ids then confidences of L * seed_rows rows, pinned mirror
-  int seed_rows = 0; int* seed_ids = nullptr; int* seed_host = nullptr;
+  int seed_rows = 0;   // rows per shadow-head call of a prompt's statistics; ids, then confidences, in the result blocks
   size_t res_ints = 0, res_words = 0;   // ints of a round's result block / all its 32-bit words (ints, then confidences)
   float* logits_dbg = nullptr; float* sink = nullptr;
   // speculative sampling: logits and fixed-point weights of the draft rows [0, d_max] and of the
@@ -149,7 +148,7 @@ struct del_ctx {
   std::vector<float> last_conf, last_draft_conf;   // like last_shadow / last_draft
   int last_stopped = 0;
   float t_draft = 0, t_verify = 0, t_shadow = 0;
-  int target_waves = 3072;
+  int target_waves = 0;       // > 0 (DEL_TARGET_WAVES): 8 waves per row block from that many row blocks / 4 on, 16 below
   int rows_form = 0;          // one-row GEMV: 1 = one row block per work-group for every matrix (DEL_ROWS_FORM)
   int wide_form = 0;          // prefill GEMMs: 1 = no k range is split over work-groups (DEL_WIDE_FORM)
   // Optional (DEL_GRAPHS=1): the segments of a round are captured once per (kind, E, gamma) into HIP
@@ -184,12 +183,26 @@ struct del_ctx {
       }
     return true;
   }
-  // waves per 16-row block: the whole k range of a block is split over the waves of its
-  // work-group; 16 waves for the matrices with few blocks, 8 when there are many
-  int pick_waves(int NB, int KT) const {
-    int w = NB * 8 >= 2 * target_waves ? 8 : 16;
+  // Waves per 16-row block (gemm_valu_k, gemm_mfma_k); the whole k range of a block is split over the waves of its
+  // work-group.  16 up to one row block per CU.  With more, smaller work-groups, so that all of them are resident at
+  // once instead of a second round that fills part of the chip; 4 where the rows are short, because staging and
+  // reduction are paid per wave.  One row, us per launch with 16 / 8 / 4 waves: 320 row blocks of 432 k tiles 32.0 /
+  // 30.1 / 30.8, 504 of 84 15.0 / 12.0 / 12.0, 1024 of 64 22.6 / 16.4 / 15.2, 8016 of 64 156 / 91 / 81; five rows: 320 of
+  // 432 38.8 / 36.7 / 36.5, 1008 of 84 25.3 / 21.0 / 19.8.  16 again where whole rounds of long rows fill the chip with
+  // one row (512 of 896 74.2 / 76.4 / 80.1).
+  int pick_waves(int NB, int KT, int m) const {
+    int w = 16;
+    if (target_waves > 0) w = NB * 8 >= 2 * target_waves ? 8 : 16;
+    else if (NB > 256 && !(m == 1 && NB % 256 == 0 && KT >= 512)) w = KT <= 96 ? 4 : 8;
     while (w > 1 && KT < 2 * w) w >>= 1;
     return w;
+  }
+  // Verification of 9 to 16 rows: a work-group of gemm_mfma_k reads 2 KiB of activation tiles with every 1 KiB weight tile,
+  // and from 100 MB of weights on the prompt passes' kernel, which shares them over 128 or 256 matrix rows, is the
+  // faster one even with half of its columns idle (13 rows, us per launch, gemm_mfma_k / gemm_wide_k: 1728 row blocks of
+  // 160 k tiles 70 / 53, 3584 of 256 215 / 165, 512 of 896 108 / 94, 320 of 432 50 / 34; 256 of 344 25.7 / 27.0).
+  bool verify_wide(const GemmP& p, int epi, int m) const {
+    return m > 8 && p.NB * (int64_t)p.KT >= 98304 && !gemm_mfma_rows_applies(p, epi, 1);
   }
 };
 
@@ -251,7 +264,6 @@ void prof_collect(del_ctx* ctx) {
 constexpr int WIDE_S = 8;   // most context splits (partials per row and head) of a wide pass's attention
 
 del_status gemm(del_ctx* ctx, GemmP p, int epi, int m, bool mfma) {
-  const int waves = ctx->pick_waves(p.NB, p.KT);
   const int64_t wbytes = (int64_t)p.NB * p.KT * 1024;
   if (mfma) {
     // blocks of up to 16 token rows, each split into tiles and multiplied on its own
@@ -267,7 +279,7 @@ del_status gemm(del_ctx* ctx, GemmP p, int epi, int m, bool mfma) {
       q.M = mb;
       const int pr = prof_begin(ctx, gemm_mfma_rows_applies(q, epi, 1) ? 5 : 1, epi, mb, wbytes);
       if (pr >= 0) { q.ev_start = ctx->prof_ev[2 * pr]; q.ev_stop = ctx->prof_ev[2 * pr + 1]; }
-      HIPCHK(launch_gemm_mfma(q, epi, waves, 1, ctx->stream));
+      HIPCHK(launch_gemm_mfma(q, epi, ctx->pick_waves(p.NB, p.KT, mb), 1, ctx->stream));
       prof_end(ctx, pr);
     }
     return DEL_OK;
@@ -287,7 +299,7 @@ del_status gemm(del_ctx* ctx, GemmP p, int epi, int m, bool mfma) {
     q.prow0 = p.prow0 + off;
     const int pr = prof_begin(ctx, gemv_rows_applies(q) ? 4 : 0, epi, g, wbytes);
     if (pr >= 0) { q.ev_start = ctx->prof_ev[2 * pr]; q.ev_stop = ctx->prof_ev[2 * pr + 1]; }
-    HIPCHK(launch_gemm_valu(q, epi, waves, ctx->stream));
+    HIPCHK(launch_gemm_valu(q, epi, ctx->pick_waves(p.NB, p.KT, g), ctx->stream));
     prof_end(ctx, pr);
     off += g;
   }
@@ -308,13 +320,25 @@ GemmP base_gemm(const del_ctx* ctx) {
 
 // Matrix-core GEMM whose input split tiles are already in p.Xs.
 del_status gemm_mf(del_ctx* ctx, GemmP p, int epi, int m) {
-  const int waves = ctx->pick_waves(p.NB, p.KT);
   p.M = m;
-  const int pr = prof_begin(ctx, gemm_mfma_rows_applies(p, epi, 1) ? 5 : 1, epi, m, (int64_t)p.NB * p.KT * 1024);
+  const bool wide = ctx->verify_wide(p, epi, m);
+  const int pr = prof_begin(ctx, wide ? 3 : gemm_mfma_rows_applies(p, epi, 1) ? 5 : 1, epi, m, (int64_t)p.NB * p.KT * 1024);
   if (pr >= 0) { p.ev_start = ctx->prof_ev[2 * pr]; p.ev_stop = ctx->prof_ev[2 * pr + 1]; }
-  HIPCHK(launch_gemm_mfma(p, epi, waves, 1, ctx->stream));
+  if (wide) {
+    p.wide_form = ctx->wide_form;
+    p.part = ctx->wide_part; p.part_bytes = ctx->wide_part_bytes;
+    HIPCHK(launch_gemm_wide(p, epi, ctx->stream));
+  } else {
+    HIPCHK(launch_gemm_mfma(p, epi, ctx->pick_waves(p.NB, p.KT, m), 1, ctx->stream));
+  }
   prof_end(ctx, pr);
   return DEL_OK;
+}
+
+// Sums of squares per token row that a residual GEMM of gemm_mf leaves: one per row block, or per four (gemm_wide_k).
+int resid_ssq_nb(const del_ctx* ctx, GemmP p, int m) {
+  p.M = m;
+  return ctx->verify_wide(p, EPI_RESID, m) ? wide_ssq_nb(p.NB) : p.NB;
 }
 
 // Transformer_l on rows [row0, row0+m) of the hidden buffer; positions T + row0 + i.
@@ -344,7 +368,9 @@ del_status run_layer(del_ctx* ctx, int l, int row0, int m, bool chained) {
   if (mf) {
     p.Xs = ctx->xs_h;
     if (chained) {
-      p.ssq_in = ctx->ssq_h; p.ssq_nb = ctx->NBd;
+      GemmP dn = base_gemm(ctx);   // the previous layer's down projection
+      dn.NB = ctx->NBd; dn.KT = ctx->KTf;
+      p.ssq_in = ctx->ssq_h; p.ssq_nb = resid_ssq_nb(ctx, dn, m);
     } else {
       HIPCHK(launch_prep_split(hin, m, m, 0, ctx->dpad, ctx->d, ctx->KTd, p.gain, 1, p.eps, ctx->xs_h, ctx->rowscale,
                                ctx->stream));
@@ -412,9 +438,11 @@ del_status run_layer(del_ctx* ctx, int l, int row0, int m, bool chained) {
     p.att_PM = ctx->PM; p.att_PL = ctx->PL; p.att_PA = ctx->PA;
     p.att_S = dec_S; p.att_stride = ctx->nch_max; p.att_hd = ctx->hd;
   }
+  int ssq_nb = ctx->NBd;
   if (mf) {
     p.Xs = ctx->xs_attn;
     p.XsOut = ctx->xs_h1; p.gain_out = ctx->gain_ffn(li); p.ssq_out = ctx->ssq_h1;
+    ssq_nb = resid_ssq_nb(ctx, p, m);
     st = gemm_mf(ctx, p, EPI_RESID, m);
   } else {
     st = gemm(ctx, p, EPI_RESID, m, false);
@@ -426,7 +454,7 @@ del_status run_layer(del_ctx* ctx, int l, int row0, int m, bool chained) {
   p.X = hout; p.ldx = ctx->dpad; p.gain = ctx->gain_ffn(li); p.rms = 1;
   p.ACT = ctx->act; p.ldact = ctx->fpad; p.d_ffn = ctx->f;
   if (mf) {
-    p.Xs = ctx->xs_h1; p.ssq_in = ctx->ssq_h1; p.ssq_nb = ctx->NBd;
+    p.Xs = ctx->xs_h1; p.ssq_in = ctx->ssq_h1; p.ssq_nb = ssq_nb;
     p.XsOut = ctx->xs_act;
     st = gemm_mf(ctx, p, EPI_SWIGLU, m);
   } else {
@@ -597,12 +625,11 @@ void free_all(del_ctx* c) {
                   c->rope, c->hid, c->q, c->attn, c->act, c->xs_layer, c->xs_shadow, c->rowscale, c->xs_h, c->xs_attn,
                   c->xs_h1, c->xs_act, c->ssq_h, c->ssq_h1, c->PM, c->PL,
                   c->PA, c->pval, c->pidx, c->psum, c->state, c->draft_ids, c->shadow_ids, c->result, c->ids_dev,
-                  c->logits_dbg, c->sink, c->stage, c->slog, c->swf, c->srows, c->unif_dev, c->rowscale_w, c->vct, c->wide_part, c->seed_ids};
+                  c->logits_dbg, c->sink, c->stage, c->slog, c->swf, c->srows, c->unif_dev, c->rowscale_w, c->vct, c->wide_part};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->result_host) (void)hipHostFree(c->result_host);   // conf_host and conf_dev point into the result blocks
   if (c->step_host) (void)hipHostFree(c->step_host);
-  if (c->seed_host) (void)hipHostFree(c->seed_host);
   for (auto& e : c->ev)
     if (e) (void)hipEventDestroy(e);
   for (auto& e : c->prof_ev)
@@ -830,11 +857,11 @@ del_status del_create(const del_config* cfg, void* hip_stream, del_ctx** out) {
     CK(dmalloc(&ctx->ssq_h, CBmax * 16 * ctx->NBd * 4));
     CK(dmalloc(&ctx->ssq_h1, CBmax * 16 * ctx->NBd * 4));
     CK(dmalloc(&ctx->rowscale_w, CBmax * 16 * 4));
-    // the workspace that the widest of all passes asks for (a pass may have any number of rows up to prows)
+    // the workspace that the widest of all passes asks for (a pass may have any number of rows up to prows; verification
+    // of up to 16 rows takes the same kernel for large matrices)
     const int shapes[4][2] = {{ctx->NBqkv, ctx->KTd}, {ctx->NBd, ctx->KTq}, {ctx->NBgu, ctx->KTd}, {ctx->NBd, ctx->KTf}};
     for (const auto& sh : shapes)
-      for (int m = 16; m <= ctx->prows; m += 16)
-        ctx->wide_part_bytes = std::max(ctx->wide_part_bytes, wide_part_bytes(wide_plan(sh[0], sh[1], m, ctx->wide_form == 1)));
+      ctx->wide_part_bytes = std::max(ctx->wide_part_bytes, wide_part_most(sh[0], sh[1], std::max(16, ctx->prows), ctx->wide_form == 1));
     if (ctx->wide_part_bytes) CK(dmalloc(&ctx->wide_part, ctx->wide_part_bytes));
     const char* fl = getenv("DEL_PREFILL_FLASH");
     if (ctx->prows > 0 && (ctx->hd == 64 || ctx->hd == 128) && !(fl && atoi(fl) == 0)) {
@@ -848,8 +875,6 @@ del_status del_create(const del_config* cfg, void* hip_stream, del_ctx** out) {
   // whole window of the paper (32 positions) where a wide pass holds it
   ctx->seed_rows = ctx->prows >= 32 ? std::max(16, std::min(32, cfg->prefill_window)) : 16;
   const int Rall = ctx->L * std::max(ctx->maxrows, ctx->seed_rows);
-  CK(dmalloc(&ctx->seed_ids, (size_t)2 * ctx->L * ctx->seed_rows * 4));
-  CK(hipHostMalloc((void**)&ctx->seed_host, (size_t)2 * ctx->L * ctx->seed_rows * 4, hipHostMallocDefault));
   const size_t xs_sh = (size_t)ceil_div(Rall, 16) * ctx->KTd * 2048;
   CK(dmalloc(&ctx->xs_shadow, xs_sh));
   CK(hipMemsetAsync(ctx->xs_shadow, 0, xs_sh, ctx->stream));
@@ -872,10 +897,11 @@ del_status del_create(const del_config* cfg, void* hip_stream, del_ctx** out) {
   // (ints), then the shadow and draft confidences (floats); the same layout in pinned host memory
   ctx->res_ints = (size_t)(3 + cfg->d_max + 1 + Rmax);
   ctx->res_words = ctx->res_ints + (size_t)(Rmax + cfg->d_max + 1);
-  CK(dmalloc(&ctx->result, ctx->res_words * 4));
+  const size_t block_bytes = std::max(ctx->res_words, (size_t)2 * ctx->L * ctx->seed_rows) * 4;   // a prompt's groups use it too
+  CK(dmalloc(&ctx->result, block_bytes));
   ctx->conf_dev = reinterpret_cast<float*>(ctx->result + ctx->res_ints);
   CK(dmalloc(&ctx->ids_dev, (size_t)ctx->Tcap * 4));
-  CK(hipHostMalloc((void**)&ctx->result_host, ctx->res_words * 4, hipHostMallocDefault));
+  CK(hipHostMalloc((void**)&ctx->result_host, block_bytes, hipHostMallocDefault));
   ctx->conf_host = reinterpret_cast<float*>(ctx->result_host + ctx->res_ints);
   CK(dmalloc(&ctx->logits_dbg, (size_t)ctx->NBv * 16 * 4));
   CK(dmalloc(&ctx->sink, 16));
@@ -1004,15 +1030,15 @@ del_status del_prefill(del_ctx* ctx, const int32_t* prompt, int32_t n_prompt, in
     // rows of this pass inside the statistics window, in groups
     for (int r0 = std::max(0, P - w - start); r0 < mc; r0 += ctx->seed_rows) {
       const int cnt = std::min(ctx->seed_rows, mc - r0);
-      del_status st = shadow_head(ctx, cnt, r0, ctx->seed_ids, reinterpret_cast<float*>(ctx->seed_ids + (size_t)L * cnt));
+      del_status st = shadow_head(ctx, cnt, r0, ctx->result, reinterpret_cast<float*>(ctx->result + (size_t)L * cnt));
       if (st != DEL_OK) return st;
-      HIPCHK(hipMemcpyAsync(ctx->seed_host, ctx->seed_ids, (size_t)2 * L * cnt * 4, hipMemcpyDeviceToHost, ctx->stream));
+      HIPCHK(hipMemcpyAsync(ctx->result_host, ctx->result, (size_t)2 * L * cnt * 4, hipMemcpyDeviceToHost, ctx->stream));
       HIPCHK(hipStreamSynchronize(ctx->stream));
-      const float* seed_conf = reinterpret_cast<const float*>(ctx->seed_host + (size_t)L * cnt);
+      const float* seed_conf = reinterpret_cast<const float*>(ctx->result_host + (size_t)L * cnt);
       for (int i = 0; i < cnt; ++i) {
         const int wpos = start + r0 + i - (P - w);
         for (int l = 1; l <= L; ++l) {
-          shadow[(size_t)(l - 1) * w + wpos] = ctx->seed_host[(l - 1) * cnt + i];
+          shadow[(size_t)(l - 1) * w + wpos] = ctx->result_host[(l - 1) * cnt + i];
           sconf[(size_t)(l - 1) * w + wpos] = seed_conf[(l - 1) * cnt + i];
         }
       }

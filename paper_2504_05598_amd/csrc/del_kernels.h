@@ -108,8 +108,9 @@ struct AttnP {
 
 hipError_t launch_gemm_valu(const GemmP& p, int epi, int waves, hipStream_t s);
 // Which kernel the two launchers here take for p: the forms with several row blocks per work-group
-// (gemv_rows_k: one row, bf16, 128, 160 or 256 k tiles, at least 256 row blocks; gemm_mfma_rows_k: up to 16 rows,
-// 128 k tiles, at least 256 row blocks, any epilogue but the residual one), unless p.rows_form == 1.
+// (gemv_rows_k: one row, bf16, 128, 160 or 256 k tiles, at least 256 row blocks; gemm_mfma_rows_k: up to 8 rows, 128
+// or 160 k tiles, or up to 16 rows, 128 k tiles and any epilogue but the residual one; at least 256 row blocks), unless
+// p.rows_form == 1.
 bool gemv_rows_applies(const GemmP& p);
 bool gemm_mfma_rows_applies(const GemmP& p, int epi, int col_blocks);
 hipError_t launch_gemm_mfma(const GemmP& p, int epi, int waves, int col_blocks, hipStream_t s);
@@ -121,6 +122,7 @@ struct WidePlan {
 };
 WidePlan wide_plan(int NB, int KT, int M, int whole);   // whole = 1: no splits
 size_t wide_part_bytes(const WidePlan& w);              // workspace a launch with this plan needs (p.part)
+size_t wide_part_most(int NB, int KT, int M, int whole);   // the most that plans for 1..M token rows need
 // epi: EPI_RESID (ssq_out: wide_ssq_nb(NB) numbers per token row), EPI_QKV or EPI_SWIGLU (split tiles only).  The RMS
 // scale comes from ssq_in / ssq_nb or from rowscale.
 hipError_t launch_gemm_wide(const GemmP& p, int epi, hipStream_t s);                      // with wide_plan's plan

@@ -335,31 +335,7 @@ __global__ void __launch_bounds__(64 * ValuWaves<M>::max) gemm_valu_k(GemmP p) {
       xv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
       gv[j] = make_float4(1.f, 1.f, 1.f, 1.f);
       if (k < Kp) {
-        if (p.att_S > 0) {
-          // the input row is the attention output: merge the S per-split softmax partials here
-          // (split by split, in a loop: the batched request of gemv_rows_k would cost this kernel, whose other
-          // instantiations run at the register limit, spills)
-          if (k < p.K) {
-            const int h = k / p.att_hd, d = k - h * p.att_hd;
-            const float* pm = p.att_PM + (size_t)h * p.att_stride;
-            const float* pl = p.att_PL + (size_t)h * p.att_stride;
-            float mx = -INFINITY;
-            for (int sidx = 0; sidx < p.att_S; ++sidx) mx = fmaxf(mx, pm[sidx]);
-            float L = 0.f;
-            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int sidx = 0; sidx < p.att_S; ++sidx) {
-              const float ms = pm[sidx];
-              const float c = ms > -INFINITY ? expf(ms - mx) : 0.f;
-              L += c * pl[sidx];
-              const float4 t = *(const float4*)(p.att_PA + ((size_t)h * p.att_stride + sidx) * p.att_hd + d);
-              a.x += c * t.x; a.y += c * t.y; a.z += c * t.z; a.w += c * t.w;
-            }
-            const float inv = 1.0f / L;
-            xv[j] = make_float4(a.x * inv, a.y * inv, a.z * inv, a.w * inv);
-          }
-        } else {
-          xv[j] = *(const float4*)(p.X + k);
-        }
+        xv[j] = *(const float4*)(p.X + k);
         if (has_gain) gv[j] = *(const float4*)(p.gain + k);
       }
     }
@@ -375,7 +351,17 @@ __global__ void __launch_bounds__(64 * ValuWaves<M>::max) gemm_valu_k(GemmP p) {
       }
     }
   };
-  if (M == 1) stage_load(tid * 4);
+  // the output projection's input row may be the attention output, still in per-split partials: those of a thread's first
+  // four features are asked for here, all at once, and merged when the tile requests are out (merged split by split in
+  // a loop ahead of them, each split cost a memory round trip)
+  const bool att = M == 1 && EPI == EPI_RESID && p.att_S > 0;
+  AttReq rq;
+  if (att) att_request(p, tid * 4, rq);
+  else if (M == 1) stage_load(tid * 4);
+  // one row: the residual, too, is requested up front (asked for in the epilogue it adds a memory round trip to every
+  // launch: 0.8 us of the 5.3 a small matrix takes)
+  float res = 0.f;
+  if (M == 1 && EPI == EPI_RESID && tid < 16 && nb * 16 + tid < p.N) res = p.R[nb * 16 + tid];
   uint4 ta[GU], tb[GU];
   if (ngroups > 0) {
 #pragma unroll
@@ -388,10 +374,19 @@ __global__ void __launch_bounds__(64 * ValuWaves<M>::max) gemm_valu_k(GemmP p) {
   if (M == 1) {
     // four 16-byte pieces per thread and batch: one batch covers 16 floats x threads, i.e. the whole row
     // for every shape but the widest rows on the smaller work-groups
-    stage_store(tid * 4);
-    for (int base = tid * 4 + 4 * stride; base < Kp; base += 4 * stride) {
-      stage_load(base);
-      stage_store(base);
+    if (att) {
+      for (int k = tid * 4; k < Kp; k += stride) {
+        if (k != tid * 4) att_request(p, k, rq);
+        const float4 x = att_merge(p, k, rq);
+        ss[0] += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+        *(float4*)(xs + k) = x;
+      }
+    } else {
+      stage_store(tid * 4);
+      for (int base = tid * 4 + 4 * stride; base < Kp; base += 4 * stride) {
+        stage_load(base);
+        stage_store(base);
+      }
     }
     __syncthreads();
   }
@@ -460,10 +455,11 @@ __global__ void __launch_bounds__(64 * ValuWaves<M>::max) gemm_valu_k(GemmP p) {
       for (int w = 0; w < nw; ++w) q += ssr[w][mi];
       s *= 1.0f / sqrtf(q / (float)p.K + p.eps);
     }
-    fin[mi][r] = s;
+    fin[mi][r] = M == 1 && EPI == EPI_RESID ? s + res : s;
   }
   __syncthreads();
-  epilogue<EPI, KPL == 8>(p, nb, fin, M, 0, p.XsOut, p.ssq_out);
+  // (a row's residual is added by now; its split tiles are for the matrix-core path only)
+  epilogue<M == 1 && EPI == EPI_RESID ? EPI_STORE : EPI, KPL == 8>(p, nb, fin, M, 0, p.XsOut, p.ssq_out);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -563,7 +559,7 @@ __global__ void __launch_bounds__(1024) gemv_rows_k(GemmP p) {
   // the finished row block: partial sums of the waves through LDS, then wave 0 alone runs the epilogue on its own
   // LDS patch while the other waves go on with the next row block (the patch is free again by then: wave 0 comes
   // back to it only after the next barrier)
-  auto finish = [&](float a, int nb) {
+  auto finish = [&](float a, int nb, float res) {
     a += __shfl_xor(a, 16);
     a += __shfl_xor(a, 32);
     if (lane < 16) red[par][wave][lane] = a;
@@ -573,10 +569,10 @@ __global__ void __launch_bounds__(1024) gemv_rows_k(GemmP p) {
       if (lane < 16) {
         float s = 0.f;
         for (int w = 0; w < ROWS_WAVES; ++w) s += red[par][w][lane];
-        fin[0][lane] = s * scale;
+        fin[0][lane] = s * scale + res;
       }
       __builtin_amdgcn_wave_barrier();
-      epilogue<EPI, true, true>(p, nb, fin, 1, 0, nullptr, nullptr);
+      epilogue<EPI == EPI_RESID ? EPI_STORE : EPI, true, true>(p, nb, fin, 1, 0, nullptr, nullptr);
       __builtin_amdgcn_wave_barrier();
     }
     par ^= 1;
@@ -584,6 +580,9 @@ __global__ void __launch_bounds__(1024) gemv_rows_k(GemmP p) {
   // one row block; `more` (fixed per call site): the refills go on into the next row block
   auto block = [&](int nb, bool more) {
     float acc[1] = {0.f};
+    // the row block's residual, asked for ahead of its products (by every wave: no branch around a load)
+    float res = 0.f;
+    if (EPI == EPI_RESID) res = p.R[min(nb * 16 + (lane & 15), p.N - 1)];
     const uint4* wn = wp + blk_stride;
 #pragma unroll
     for (int gi = 0; gi < NG; gi += 2) {
@@ -598,7 +597,7 @@ __global__ void __launch_bounds__(1024) gemv_rows_k(GemmP p) {
       else if (more) fill(tb, wn + GUX * 64);
       __builtin_amdgcn_sched_barrier(0);
     }
-    finish(acc[0], nb);
+    finish(acc[0], nb, res);
     wp = wn;
   };
   int nb = wg;
@@ -610,9 +609,23 @@ __global__ void __launch_bounds__(1024) gemv_rows_k(GemmP p) {
 // Matrix-core skinny GEMM (bf16 weights): out[16 weight rows][16 token rows] per wave via
 // v_mfma_f32_16x16x32_bf16, weights as the A operand straight from the tiled layout, token
 // rows as the B operand from hi/lo split tiles ([cb][kt][hi|lo][lane][8], lane = 16*(k/8%4) +
-// token).  Two MFMAs per tile (hi, lo).  blockIdx.y selects a block of 16 token rows.
+// token).  blockIdx.y selects a block of 16 token rows.
+// PACK (up to 8 token rows): the high parts are columns 0..7 of the operand and the low parts columns 8..15, so that one
+// load and one matrix instruction per weight tile do (against two of each), and column c + 8 is added to column c with
+// the waves' partial sums.  What bounds the kernel is how many weight tiles a wave keeps in flight, and the activation
+// tiles took two of every three loads.  5 rows, us per launch, separate -> packed: 1376 row blocks of 128 k tiles 33.9 -> 32.8
+// (several row blocks per work-group, below), 256 of 344 21.1 -> 20.5, 1728 of 160 52.9 -> 47.3, 320 of 432 40.3 -> 36.7
+// (with 8 waves instead of 16), 512 of 896 81.8 -> 77.5; 8 rows gain more (512 of 896: 108 -> 77).
 // ---------------------------------------------------------------------------------------
-template <int EPI>
+// The piece of a 2 KiB activation tile that a lane supplies; rows beyond the valid ones repeat row 0 (no divergent loads,
+// the same cache lines; their columns are never used).
+template <bool PACK>
+__device__ __forceinline__ int act_piece(int lane, int mvalid) {
+  const int c = lane & 15, t = PACK ? c & 7 : c;
+  return (PACK && c >= 8 ? 64 : 0) + (lane & 48) + (t < mvalid ? t : 0);
+}
+
+template <int EPI, bool PACK>
 __global__ void __launch_bounds__(1024) gemm_mfma_k(GemmP p) {
   constexpr int U = 4;
   __shared__ float red[MAXW][16][16];
@@ -622,10 +635,7 @@ __global__ void __launch_bounds__(1024) gemm_mfma_k(GemmP p) {
   const int nb = blockIdx.x, cb = blockIdx.y;
   const int mvalid = min(16, p.M - cb * 16);
   const int token = lane & 15, g = lane >> 4;
-  // Lanes of token rows beyond the valid ones read the tile of token row 0 of their k group
-  // (same cache lines as the active lanes, no extra traffic, no divergent loads); their output
-  // columns are never used.
-  const int blane = token < mvalid ? lane : (lane & 48);
+  const int blane = act_piece<PACK>(lane, mvalid);
   int kt_lo, kt_hi;
   wave_span(p.KT, nw, wave, U, kt_lo, kt_hi);
   const int ngroups = (kt_hi - kt_lo) / U;
@@ -634,7 +644,7 @@ __global__ void __launch_bounds__(1024) gemm_mfma_k(GemmP p) {
   floatx4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};   // hi and lo products, independent chains
   // two register sets (even and odd groups), never copied: a copy of a register that a load is still
   // filling would make the wave wait for every load in flight
-  uint4 a0[U], h0[U], l0[U], a1[U], h1[U], l1[U];
+  uint4 a0[U], h0[U], l0[PACK ? 1 : U], a1[U], h1[U], l1[PACK ? 1 : U];
   auto fill = [&](uint4* a, uint4* bh, uint4* bl, int gi) {
     const uint4* wn = wp + (size_t)gi * U * 64;
     const uint4* xn = xp + (size_t)gi * U * 128;
@@ -642,15 +652,20 @@ __global__ void __launch_bounds__(1024) gemm_mfma_k(GemmP p) {
     for (int u = 0; u < U; ++u) {
       a[u] = ld_stream(wn + u * 64);
       bh[u] = xn[u * 128];
-      bl[u] = xn[u * 128 + 64];
+      if (!PACK) bl[u] = xn[u * 128 + 64];
     }
   };
   auto use = [&](const uint4* a, const uint4* bh, const uint4* bl) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bf16x8 av = __builtin_bit_cast(bf16x8, a[u]);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bh[u]), acc, 0, 0, 0);
-      acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bl[u]), acc2, 0, 0, 0);
+      if (PACK) {   // two chains, tiles in turn
+        floatx4& c = u & 1 ? acc2 : acc;
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bh[u]), c, 0, 0, 0);
+      } else {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bh[u]), acc, 0, 0, 0);
+        acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bl[u]), acc2, 0, 0, 0);
+      }
     }
   };
   if (ngroups > 0) fill(a0, h0, l0, 0);
@@ -685,10 +700,13 @@ __global__ void __launch_bounds__(1024) gemm_mfma_k(GemmP p) {
   }
   for (int kt = kt_lo + ngroups * U; kt < kt_hi; ++kt) {
     const uint4 aw = ld_stream(wp + (size_t)(kt - kt_lo) * 64);
-    const uint4 h = xp[(size_t)(kt - kt_lo) * 128], l = xp[(size_t)(kt - kt_lo) * 128 + 64];
+    const uint4 h = xp[(size_t)(kt - kt_lo) * 128];
     const bf16x8 av = __builtin_bit_cast(bf16x8, aw);
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, h), acc, 0, 0, 0);
-    acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, l), acc2, 0, 0, 0);
+    if (!PACK) {
+      const uint4 l = xp[(size_t)(kt - kt_lo) * 128 + 64];
+      acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, l), acc2, 0, 0, 0);
+    }
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) acc[j] += acc2[j];
@@ -700,7 +718,7 @@ __global__ void __launch_bounds__(1024) gemm_mfma_k(GemmP p) {
     const int mi = t >> 4, r = t & 15;
     if (mi < mvalid) {
       float s = 0.f;
-      for (int w = 0; w < nw; ++w) s += red[w][mi][r];
+      for (int w = 0; w < nw; ++w) s += PACK ? red[w][mi][r] + red[w][mi + 8][r] : red[w][mi][r];
       if (p.rowscale) s *= p.rowscale[cb * 16 + mi];
       if (p.ssq_in) s *= scl[mi];
       fin[mi][r] = s;
@@ -711,17 +729,18 @@ __global__ void __launch_bounds__(1024) gemm_mfma_k(GemmP p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// The matrix-core skinny GEMM with several row blocks per work-group (up to 16 token rows, KT = 128):
-// as gemv_rows_k, one work-group of 16 waves per compute unit taking the row blocks w, w + grid, ...  A wave
-// owns 8 k tiles of every row block; the split activation tiles of those 8 k tiles do not depend on the row
-// block, so they are loaded once and stay in registers for all of the work-group's row blocks (the form
-// above fetches them again with every weight tile: two of its three loads).  Weight tiles: two named sets
-// of 4, refilled as soon as used, running on into the next row block.  Wave 0 sums the waves' 16x16 partials
-// and runs the epilogue while the others go on.
+// The matrix-core skinny GEMM with several row blocks per work-group (up to 16 token rows, KT = 16 * NT: 128 or 160 k
+// tiles): as gemv_rows_k, one work-group of 16 waves per compute unit taking the row blocks w, w + grid, ...  A wave
+// owns NT k tiles of every row block; the split activation tiles of those k tiles do not depend on the row block, so
+// they are loaded once and stay in registers for all of the work-group's row blocks (the form above fetches them again
+// with every weight tile).  Weight tiles: two named sets of HS, refilled as soon as used, running on into the next row
+// block; 16 waves per work-group cap a wave at 128 registers, so that with separate high and low parts (more than 8
+// token rows) only NT = 8 fits, with sets of 2; packed, a tile is 4 registers and the sets are as deep as the one-row
+// kernel's.  Wave 0 sums the waves' 16x16 partials and runs the epilogue while the others go on.
 // ---------------------------------------------------------------------------------------
-template <int EPI>
+template <int EPI, bool PACK, int NT, int HS>
 __global__ void __launch_bounds__(1024) gemm_mfma_rows_k(GemmP p) {
-  constexpr int NG = 2;
+  static_assert(NT % (2 * HS) == 0, "the two sets take the tiles in turn");
   __shared__ float red[2][ROWS_WAVES][16][16];
   __shared__ float fin[16][16];
   __shared__ float scl[16];
@@ -729,24 +748,21 @@ __global__ void __launch_bounds__(1024) gemm_mfma_rows_k(GemmP p) {
   const int wg = blockIdx.x, nwg = gridDim.x;
   if (wg >= p.NB) return;                                // uniform, before any barrier
   const int nblk = (p.NB - wg + nwg - 1) / nwg;
-  const int KT = p.KT;                                   // = 128
+  const int KT = p.KT;                                   // = 16 * NT
   const int mvalid = min(16, p.M);
   const int token = lane & 15, g = lane >> 4;
-  const int blane = token < mvalid ? lane : (lane & 48);   // lanes of rows beyond the valid ones re-read token row 0
-  const int lo_t = wave * NG * GU;
-  // this wave's activation tiles (high and low parts) for its 8 k tiles: loaded once
-  uint4 bh[NG * GU], bl[NG * GU];
+  const int blane = act_piece<PACK>(lane, mvalid);
+  const int lo_t = wave * NT;
+  // this wave's activation tiles for its k tiles: loaded once
+  uint4 bh[NT], bl[PACK ? 1 : NT];
   const uint4* xp = (const uint4*)p.Xs + (size_t)lo_t * 128 + blane;
 #pragma unroll
-  for (int i = 0; i < NG * GU; ++i) {
+  for (int i = 0; i < NT; ++i) {
     bh[i] = xp[i * 128];
-    bl[i] = xp[i * 128 + 64];
+    if (!PACK) bl[i] = xp[i * 128 + 64];
   }
   const size_t blk_stride = (size_t)nwg * KT * 64;
   const uint4* wp = (const uint4*)p.Wt + ((size_t)wg * KT + lo_t) * 64 + lane;
-  // weight tiles: two named sets of HS = 2 tiles (the activation tiles leave registers for no more: 16 waves per
-  // work-group cap a wave at 128), each refilled as soon as used
-  constexpr int HS = 2;
   uint4 ta[HS], tb[HS];
   auto fill = [&](uint4* t, const uint4* src) {
 #pragma unroll
@@ -776,7 +792,7 @@ __global__ void __launch_bounds__(1024) gemm_mfma_rows_k(GemmP p) {
         const int t = lane + 64 * i, mi = t >> 4, r = t & 15;
         if (mi < mvalid) {
           float s = 0.f;
-          for (int w = 0; w < ROWS_WAVES; ++w) s += red[par][w][mi][r];
+          for (int w = 0; w < ROWS_WAVES; ++w) s += PACK ? red[par][w][mi][r] + red[par][w][mi + 8][r] : red[par][w][mi][r];
           if (p.rowscale) s *= p.rowscale[mi];
           if (p.ssq_in) s *= scl[mi];
           fin[mi][r] = s;
@@ -796,10 +812,9 @@ __global__ void __launch_bounds__(1024) gemm_mfma_rows_k(GemmP p) {
       for (int u = 0; u < HS; ++u) {
         const bf16x8 av = __builtin_bit_cast(bf16x8, t[u]);
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bh[i0 + u]), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bl[i0 + u]), acc, 0, 0, 0);
+        if (!PACK) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bl[i0 + u]), acc, 0, 0, 0);
       }
     };
-    constexpr int NT = NG * GU;   // this wave's tiles of a row block
 #pragma unroll
     for (int i0 = 0; i0 < NT; i0 += 2 * HS) {
       use(ta, i0);
@@ -1753,68 +1768,55 @@ bool gemv_rows_applies(const GemmP& p) {
   return p.wdtype == 1 && p.M == 1 && p.rows_form != 1 && p.NB >= ROWS_GRID && !p.XsOut && (p.KT == 128 || p.KT == 160 || p.KT == 256);
 }
 bool gemm_mfma_rows_applies(const GemmP& p, int epi, int col_blocks) {
-  // (not with the residual epilogue: that instantiation does not fit 128 registers, and its matrices have one row
-  // block per work-group anyway)
-  return col_blocks == 1 && p.KT == 128 && p.NB >= ROWS_GRID && p.rows_form != 1 && epi != EPI_RESID;
+  // (not with the residual epilogue and separate high and low parts: that instantiation does not fit 128 registers)
+  const bool pack = p.M <= 8;
+  return col_blocks == 1 && p.NB >= ROWS_GRID && p.rows_form != 1 &&
+         (pack ? p.KT == 128 || p.KT == 160 : p.KT == 128 && epi != EPI_RESID);
 }
 
 hipError_t launch_gemm_valu(const GemmP& p, int epi, int waves, hipStream_t s) {
   if (waves < 1 || waves > MAXW || p.NB <= 0 || p.KT <= 0) return hipErrorInvalidValue;
-  // attention partials as the input row: at most ATT_SMAX splits, whole float4 groups of features inside a head
-  if (p.att_S > 0 && (p.att_S > ATT_SMAX || p.att_S > p.att_stride || p.K < 4 || p.att_hd % 4 || p.K % p.att_hd ||
-                      !p.att_PM || !p.att_PL || !p.att_PA))
+  // attention partials as the input row: the output projection (no gain), at most ATT_SMAX splits, whole float4 groups of
+  // features inside a head
+  if (p.att_S > 0 && (epi != EPI_RESID || p.gain || p.att_S > ATT_SMAX || p.att_S > p.att_stride || p.K < 4 || p.att_hd % 4 ||
+                      p.K % p.att_hd || !p.att_PM || !p.att_PL || !p.att_PA))
     return hipErrorInvalidValue;
   if (gemv_rows_applies(p))
     return p.KT == 128 ? launch_rows<2>(p, epi, s) : p.KT == 160 ? launch_rows<2, 5>(p, epi, s) : launch_rows<4>(p, epi, s);
   return p.wdtype == 1 ? launch_valu_k<8>(p, epi, waves, s) : launch_valu_k<4>(p, epi, waves, s);
 }
 
+template <int EPI>
+static hipError_t launch_mfma_e(const GemmP& p, int waves, int col_blocks, hipStream_t s) {
+  const dim3 grid(p.NB, col_blocks), block(64 * waves), rgrid(ROWS_GRID), rblock(64 * ROWS_WAVES);
+  const bool pack = p.M <= 8;
+#define MFMA_GO(K, GR, BL) hipExtLaunchKernelGGL(K, GR, BL, 0, s, p.ev_start, p.ev_stop, 0, p)
+  if (gemm_mfma_rows_applies(p, EPI, col_blocks)) {
+    // several row blocks per work-group, the activation tiles held in registers
+    if (pack && p.KT == 128) MFMA_GO((gemm_mfma_rows_k<EPI, true, 8, 4>), rgrid, rblock);
+    else if (pack) MFMA_GO((gemm_mfma_rows_k<EPI, true, 10, 5>), rgrid, rblock);
+    else if constexpr (EPI != EPI_RESID) MFMA_GO((gemm_mfma_rows_k<EPI, false, 8, 2>), rgrid, rblock);
+  } else if (pack) {
+    MFMA_GO((gemm_mfma_k<EPI, true>), grid, block);
+  } else {
+    MFMA_GO((gemm_mfma_k<EPI, false>), grid, block);
+  }
+#undef MFMA_GO
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_mfma(const GemmP& p, int epi, int waves, int col_blocks, hipStream_t s) {
   if (waves < 1 || waves > MAXW || p.NB <= 0 || p.KT <= 0 || p.wdtype != 1 || col_blocks < 1 ||
       p.M > col_blocks * 16 || p.M <= (col_blocks - 1) * 16)
     return hipErrorInvalidValue;
-  const bool timed = p.ev_start && p.ev_stop;
-  if (gemm_mfma_rows_applies(p, epi, col_blocks)) {
-    // several row blocks per work-group, the activation tiles held in registers
-    const dim3 rgrid(ROWS_GRID), rblock(64 * ROWS_WAVES);
-#define MFMA_ROWS(E)                                                                                              \
-  if (timed) hipExtLaunchKernelGGL((gemm_mfma_rows_k<E>), rgrid, rblock, 0, s, p.ev_start, p.ev_stop, 0, p);       \
-  else hipLaunchKernelGGL((gemm_mfma_rows_k<E>), rgrid, rblock, 0, s, p);                                           \
-  return hipGetLastError();
-    switch (epi) {
-      case EPI_STORE: MFMA_ROWS(EPI_STORE)
-      case EPI_QKV: MFMA_ROWS(EPI_QKV)
-      case EPI_SWIGLU: MFMA_ROWS(EPI_SWIGLU)
-      case EPI_ARGMAX: MFMA_ROWS(EPI_ARGMAX)
-      default: return hipErrorInvalidValue;
-    }
-#undef MFMA_ROWS
-  }
-  dim3 grid(p.NB, col_blocks), block(64 * waves);
   switch (epi) {
-    case EPI_STORE:
-      if (timed) hipExtLaunchKernelGGL((gemm_mfma_k<EPI_STORE>), grid, block, 0, s, p.ev_start, p.ev_stop, 0, p);
-      else hipLaunchKernelGGL((gemm_mfma_k<EPI_STORE>), grid, block, 0, s, p);
-      break;
-    case EPI_RESID:
-      if (timed) hipExtLaunchKernelGGL((gemm_mfma_k<EPI_RESID>), grid, block, 0, s, p.ev_start, p.ev_stop, 0, p);
-      else hipLaunchKernelGGL((gemm_mfma_k<EPI_RESID>), grid, block, 0, s, p);
-      break;
-    case EPI_QKV:
-      if (timed) hipExtLaunchKernelGGL((gemm_mfma_k<EPI_QKV>), grid, block, 0, s, p.ev_start, p.ev_stop, 0, p);
-      else hipLaunchKernelGGL((gemm_mfma_k<EPI_QKV>), grid, block, 0, s, p);
-      break;
-    case EPI_SWIGLU:
-      if (timed) hipExtLaunchKernelGGL((gemm_mfma_k<EPI_SWIGLU>), grid, block, 0, s, p.ev_start, p.ev_stop, 0, p);
-      else hipLaunchKernelGGL((gemm_mfma_k<EPI_SWIGLU>), grid, block, 0, s, p);
-      break;
-    case EPI_ARGMAX:
-      if (timed) hipExtLaunchKernelGGL((gemm_mfma_k<EPI_ARGMAX>), grid, block, 0, s, p.ev_start, p.ev_stop, 0, p);
-      else hipLaunchKernelGGL((gemm_mfma_k<EPI_ARGMAX>), grid, block, 0, s, p);
-      break;
+    case EPI_STORE: return launch_mfma_e<EPI_STORE>(p, waves, col_blocks, s);
+    case EPI_RESID: return launch_mfma_e<EPI_RESID>(p, waves, col_blocks, s);
+    case EPI_QKV: return launch_mfma_e<EPI_QKV>(p, waves, col_blocks, s);
+    case EPI_SWIGLU: return launch_mfma_e<EPI_SWIGLU>(p, waves, col_blocks, s);
+    case EPI_ARGMAX: return launch_mfma_e<EPI_ARGMAX>(p, waves, col_blocks, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_prep_split(const float* src, int rows, int rows_per_group, int64_t group_stride, int ld, int K,

@@ -422,32 +422,62 @@ __global__ void __launch_bounds__(256) wide_finish_k(GemmP p, WidePlan w) {
 // E.g. 256 row blocks, 344 k tiles (7B down projection): at 1024 rows 296 us unsplit, 171 in two, 161 in four ranges;
 // at 256 rows 156 / 86 / 54 / 55 us with 1 / 2 / 4 / 8.  192 row blocks, 64 k tiles (1B QKV) at 256 rows: 20.0 us with 8
 // row blocks per wave (two ranges), 13.8 with 4 (unsplit).
-WidePlan wide_plan(int NB, int KT, int M, int whole) {
-  struct Form { int RW, CBT; double alone, shared; };   // us per k tile
-  constexpr Form forms[] = {{8, 2, 0.41, 0.25}, {8, 4, 0.55, 0.44}, {8, 8, 0.95, 0.76},
-                            {4, 2, 0.18, 0.17}, {4, 4, 0.30, 0.27}, {4, 8, 0.56, 0.46}};
-  constexpr double START_US = 3.0, LAUNCH_US = 4.0, PER_PART_US = 0.25, HBM_BYTES_PER_US = 5.5e6, PART_BYTES_PER_US = 8.0e6;
+namespace {
+
+struct Form { int RW, CBT; double alone, shared; int in_flight; };   // us per k tile; weight bytes on their way per work-group
+constexpr Form forms[] = {{8, 2, 0.41, 0.36, 49152}, {8, 4, 0.55, 0.44, 32768}, {8, 8, 0.95, 0.76, 16384},
+                          {4, 2, 0.18, 0.17, 24576}, {4, 4, 0.30, 0.27, 24576}, {4, 8, 0.56, 0.46, 16384}};
+
+// The best number of k ranges for tiles of this form, NCG side by side; *us: its time.
+WidePlan best_split(const Form& f, int NB, int KT, int NCG, int whole, double* us) {
+  constexpr double START_US = 3.0, LAUNCH_US = 4.0, PER_PART_US = 0.25, HBM_BYTES_PER_US = 5.5e6, HBM_LATENCY_US = 0.8,
+                   PART_BYTES_PER_US = 8.0e6;
   constexpr int CUS = 256, MAX_PART = 512, MAX_SPLIT = 32, MIN_KT = 4;
+  WidePlan best{};
+  *us = 1e30;
+  const int wrb = 2 * f.RW, T = (NB + wrb - 1) / wrb * NCG;
+  for (int S = 1; S <= MAX_SPLIT; ++S) {
+    const int full = S > 1 ? T / CUS * CUS : T, rem = T - full;
+    if (S > 1 && (whole || rem == 0 || S * MIN_KT > KT || rem * S > MAX_PART)) break;
+    const int wgs = (full + CUS - 1) / CUS + (rem * S + CUS - 1) / CUS;   // work-groups of the busiest CU
+    const double kts = (double)((full + CUS - 1) / CUS) * KT + (double)((rem * S + CUS - 1) / CUS) * ((KT + S - 1) / S);
+    // the weights arrive as fast as the memory delivers, or as the requests that are out at one time allow
+    const double resident = std::min(full + rem * S, 2 * CUS);
+    const double rate = std::min(HBM_BYTES_PER_US, resident / NCG * f.in_flight / HBM_LATENCY_US);
+    double t = std::max((wgs > 1 ? f.shared : f.alone) * kts, (double)NB * KT * 1024 / rate) + START_US;
+    if (S > 1) t += LAUNCH_US + PER_PART_US * S + 2.0 * rem * S * f.CBT * wrb * 1024 / PART_BYTES_PER_US;
+    if (t < *us) {
+      *us = t;
+      best = WidePlan{f.RW, f.CBT, NCG, full, rem, S};
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
+WidePlan wide_plan(int NB, int KT, int M, int whole) {
   WidePlan best{};
   double best_t = 1e30;
   const int CB = (M + 15) / 16;
   for (const Form& f : forms) {
-    const int wrb = 2 * f.RW, NCG = (CB + f.CBT - 1) / f.CBT, T = (NB + wrb - 1) / wrb * NCG;
-    for (int S = 1; S <= MAX_SPLIT; ++S) {
-      const int full = S > 1 ? T / CUS * CUS : T, rem = T - full;
-      if (S > 1 && (whole || rem == 0 || S * MIN_KT > KT || rem * S > MAX_PART)) break;
-      const int wgs = (full + CUS - 1) / CUS + (rem * S + CUS - 1) / CUS;   // work-groups of the busiest CU
-      const double kts = (double)((full + CUS - 1) / CUS) * KT + (double)((rem * S + CUS - 1) / CUS) * ((KT + S - 1) / S);
-      double t = std::max((wgs > 1 ? f.shared : f.alone) * kts, (double)NB * KT * 1024 / HBM_BYTES_PER_US);
-      t += START_US;
-      if (S > 1) t += LAUNCH_US + PER_PART_US * S + 2.0 * rem * S * f.CBT * wrb * 1024 / PART_BYTES_PER_US;
-      if (t < best_t) {
-        best_t = t;
-        best = WidePlan{f.RW, f.CBT, NCG, full, rem, S};
-      }
-    }
+    double t;
+    const WidePlan w = best_split(f, NB, KT, (CB + f.CBT - 1) / f.CBT, whole, &t);
+    if (t < best_t) { best_t = t; best = w; }
   }
   return best;
+}
+
+// The most workspace that a plan for up to M token rows asks for.
+size_t wide_part_most(int NB, int KT, int M, int whole) {
+  size_t most = 0;
+  const int CB = (M + 15) / 16;
+  for (const Form& f : forms)
+    for (int ncg = 1; ncg <= (CB + f.CBT - 1) / f.CBT; ++ncg) {
+      double t;
+      most = std::max(most, wide_part_bytes(best_split(f, NB, KT, ncg, whole, &t)));
+    }
+  return most;
 }
 
 size_t wide_part_bytes(const WidePlan& w) { return w.rem ? (size_t)w.rem * w.S * w.CBT * 2 * w.RW * 1024 : 0; }
