@@ -251,8 +251,8 @@ del_status del_debug_spec_sample(del_ctx* ctx, const float* q_logits, const floa
  * into a HIP graph, tight serving loops, harnesses that forbid hipMalloc.  The sampling arithmetic of
  * del_debug_spec_sample on logits that are already in DEVICE memory, with no context: every intermediate
  * (fixed-point weights, per-row records, counters) lives in one fixed device array of the library
- * (about 4.5 MB per GPU, held until the process ends).  The call allocates nothing, copies nothing to or
- * from the host and does not wait: it queues four kernels on `hip_stream` (NULL = default stream).
+ * (about 5.7 MB per GPU, held until the process ends).  The call allocates nothing, copies nothing to or
+ * from the host and does not wait: it queues three kernels on `hip_stream` (NULL = default stream).
  *   q_logits  device, [gamma][ld_logits] floats (may be NULL when gamma == 0); p_logits device,
  *             [gamma+1][ld_logits]; both 16-byte aligned, ld_logits a multiple of 4 and >= vocab
  *   uniforms  device, 2*gamma+1 floats in [0, 1): drafts, acceptances, last token (not checked)

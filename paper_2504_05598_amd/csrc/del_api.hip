@@ -134,6 +134,7 @@ struct del_ctx {
   // speculative sampling: logits and fixed-point weights of the draft rows [0, d_max] and of the
   // target rows [d_max+1, 2*d_max+1], one SampRow each, and the round's uniform numbers
   float* slog = nullptr; unsigned long long* swf = nullptr; SampRow* srows = nullptr; float* unif_dev = nullptr;
+  char* samp_scratch = nullptr;
   int64_t sld = 0;   // row stride of slog and swf, in elements
   void* stage = nullptr; size_t stage_bytes = 0;
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -625,7 +626,8 @@ void free_all(del_ctx* c) {
                   c->rope, c->hid, c->q, c->attn, c->act, c->xs_layer, c->xs_shadow, c->rowscale, c->xs_h, c->xs_attn,
                   c->xs_h1, c->xs_act, c->ssq_h, c->ssq_h1, c->PM, c->PL,
                   c->PA, c->pval, c->pidx, c->psum, c->state, c->draft_ids, c->shadow_ids, c->result, c->ids_dev,
-                  c->logits_dbg, c->sink, c->stage, c->slog, c->swf, c->srows, c->unif_dev, c->rowscale_w, c->vct, c->wide_part};
+                  c->logits_dbg, c->sink, c->stage, c->slog, c->swf, c->srows, c->unif_dev, c->rowscale_w, c->vct, c->wide_part,
+                  c->samp_scratch};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->result_host) (void)hipHostFree(c->result_host);   // conf_host and conf_dev point into the result blocks
@@ -911,6 +913,7 @@ del_status del_create(const del_config* cfg, void* hip_stream, del_ctx** out) {
     CK(dmalloc(&ctx->slog, srow_n * ctx->sld * 4));
     CK(dmalloc(&ctx->swf, srow_n * ctx->sld * 8));
     CK(dmalloc(&ctx->srows, srow_n * sizeof(SampRow)));
+    CK(dmalloc(&ctx->samp_scratch, srow_n * SAMP_PARTS * SAMP_PART_BYTES));
     CK(dmalloc(&ctx->unif_dev, (srow_n + 2) * 4));
   }
   for (auto& e : ctx->ev) CK(hipEventCreate(&e));
@@ -1268,6 +1271,14 @@ static del_status sample_logits(del_ctx* ctx, int layer, int row0, int m, int sr
   return gemm(ctx, p, EPI_STORE, m, mf);
 }
 
+// Sampling rows [srow0, srow0 + n).
+static SampSeg samp_seg(del_ctx* ctx, int srow0, int n) {
+  SampSeg g{};
+  g.Z = ctx->slog + (size_t)srow0 * ctx->sld; g.WF = ctx->swf + (size_t)srow0 * ctx->sld; g.rows = ctx->srows + srow0;
+  g.n = n;
+  return g;
+}
+
 static bool sampling_args_ok(double temperature, double top_p) {
   return temperature > 0.0 && top_p > 0.0 && top_p <= 1.0 && std::isfinite(temperature);
 }
@@ -1280,9 +1291,10 @@ del_status del_sample_first(del_ctx* ctx, double temperature, double top_p, floa
   del_status st = sample_logits(ctx, ctx->L, ctx->last_rows - 1, 1, VB);
   if (st != DEL_OK) return st;
   HIPCHK(hipMemcpyAsync(ctx->unif_dev, &r, 4, hipMemcpyHostToDevice, s));
-  HIPCHK(launch_samp_rowstats(ctx->slog + (size_t)VB * ctx->sld, ctx->sld, ctx->V, 1, temperature, top_p,
-                              ctx->swf + (size_t)VB * ctx->sld, ctx->sld, ctx->srows + VB, ctx->unif_dev,
-                              ctx->draft_ids, ctx->state + 1, nullptr, s));
+  SampSegs sg{};
+  sg.seg[0] = samp_seg(ctx, VB, 1);
+  sg.seg[0].draw_r = ctx->unif_dev; sg.seg[0].draw_tok = ctx->draft_ids; sg.seg[0].pending = ctx->state + 1;
+  HIPCHK(launch_samp_rowstats(sg, ctx->sld, ctx->sld, ctx->V, temperature, top_p, ctx->samp_scratch, s));
   HIPCHK(hipMemcpyAsync(ctx->step_host, ctx->draft_ids, 4, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   ctx->pending = ctx->step_host[0];
@@ -1323,9 +1335,11 @@ static del_status round_sample_impl(del_ctx* ctx, int E, int gamma, double tau, 
     if (i < gamma) {
       del_status st = sample_logits(ctx, E, i, 1, i);
       if (st != DEL_OK) return st;
-      HIPCHK(launch_samp_rowstats(ctx->slog + (size_t)i * ld, ld, V, 1, temperature, top_p, ctx->swf + (size_t)i * ld,
-                                  ld, ctx->srows + i, ctx->unif_dev + i, ctx->draft_ids + i, nullptr,
-                                  dynamic ? dconf + i : nullptr, s));
+      SampSegs sg{};
+      sg.seg[0] = samp_seg(ctx, i, 1);
+      sg.seg[0].draw_r = ctx->unif_dev + i; sg.seg[0].draw_tok = ctx->draft_ids + i;
+      sg.seg[0].conf_out = dynamic ? dconf + i : nullptr;
+      HIPCHK(launch_samp_rowstats(sg, ld, ld, V, temperature, top_p, ctx->samp_scratch, s));
       if (dynamic) {   // the host decides whether to go on: one small copy and a sync per step
         HIPCHK(hipMemcpyAsync(ctx->step_host, dconf + i, 4, hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
@@ -1353,8 +1367,9 @@ static del_status round_sample_impl(del_ctx* ctx, int E, int gamma, double tau, 
     if (st != DEL_OK) return st;
     st = sample_logits(ctx, L, 0, m, VB);
     if (st != DEL_OK) return st;
-    HIPCHK(launch_samp_rowstats(ctx->slog + (size_t)VB * ld, ld, V, m, temperature, top_p, ctx->swf + (size_t)VB * ld, ld,
-                                ctx->srows + VB, nullptr, nullptr, nullptr, nullptr, s));
+    SampSegs sg{};
+    sg.seg[0] = samp_seg(ctx, VB, m);
+    HIPCHK(launch_samp_rowstats(sg, ld, ld, V, temperature, top_p, ctx->samp_scratch, s));
     HIPCHK(launch_samp_accept(ctx->slog, ctx->swf, ctx->srows, ctx->slog + (size_t)VB * ld, ctx->swf + (size_t)VB * ld,
                               ctx->srows + VB, ld, ld, V, gamma, ctx->draft_ids, ctx->unif_dev + cap,
                               ctx->unif_dev + 2 * cap, ctx->state, ctx->shadow_ids, L * m, ctx->result, s));
@@ -1409,11 +1424,11 @@ del_status del_debug_spec_sample(del_ctx* ctx, const float* q_logits, const floa
   const size_t n_scr = (size_t)4 + DM + 3 + DM;
   if ((size_t)ctx->NBv * 16 < n_scr) return DEL_E_CAPACITY;
   HIPCHK(hipMemsetAsync(scratch, 0, n_scr * 4, s));
-  if (gamma > 0)
-    HIPCHK(launch_samp_rowstats(ctx->slog, ld, V, gamma, temperature, top_p, ctx->swf, ld, ctx->srows, ctx->unif_dev,
-                                dr_s, nullptr, nullptr, s));
-  HIPCHK(launch_samp_rowstats(ctx->slog + (size_t)VB * ld, ld, V, gamma + 1, temperature, top_p,
-                              ctx->swf + (size_t)VB * ld, ld, ctx->srows + VB, nullptr, nullptr, nullptr, nullptr, s));
+  SampSegs sg{};
+  sg.seg[0] = samp_seg(ctx, 0, gamma);
+  sg.seg[0].draw_r = ctx->unif_dev; sg.seg[0].draw_tok = dr_s;
+  sg.seg[1] = samp_seg(ctx, VB, gamma + 1);
+  HIPCHK(launch_samp_rowstats(sg, ld, ld, V, temperature, top_p, ctx->samp_scratch, s));
   HIPCHK(launch_samp_accept(ctx->slog, ctx->swf, ctx->srows, ctx->slog + (size_t)VB * ld, ctx->swf + (size_t)VB * ld,
                             ctx->srows + VB, ld, ld, V, gamma, dr_s, ctx->unif_dev + gamma, ctx->unif_dev + 2 * gamma, st_s,
                             nullptr, 0, rs_s, s));
@@ -1430,8 +1445,8 @@ del_status del_debug_spec_sample(del_ctx* ctx, const float* q_logits, const floa
 
 // ---- the entry point that allocates nothing ---------------------------------------------------------
 // Scratch of del_spec_sample_static: fixed-point weights of up to 2*8+1 logits rows of up to 32768
-// tokens, one SampRow per row, and a few integers.  One copy per GPU the library runs on, held until the
-// process ends.  Host code never uses the array's name as an address: the device address is looked up
+// tokens, one SampRow and the parts' records per row, and a few integers.  One copy per GPU the library
+// runs on, held until the process ends.  Host code never uses the array's name as an address: the device address is looked up
 // once per device with hipGetSymbolAddress and kept in static_scratch_ptr.
 namespace {
 constexpr int STATIC_MAX_VOCAB = 32768, STATIC_MAX_GAMMA = 8;
@@ -1439,7 +1454,8 @@ constexpr size_t ST_ROWS = 2 * STATIC_MAX_GAMMA + 1;
 constexpr size_t ST_WF_BYTES = ST_ROWS * (size_t)STATIC_MAX_VOCAB * sizeof(unsigned long long);
 constexpr size_t ST_SROW_BYTES = (ST_ROWS * sizeof(SampRow) + 255) / 256 * 256;
 constexpr size_t ST_INT_BYTES = 256;
-constexpr size_t ST_BYTES = ST_WF_BYTES + ST_SROW_BYTES + ST_INT_BYTES;
+constexpr size_t ST_PART_BYTES = ST_ROWS * SAMP_PARTS * (size_t)SAMP_PART_BYTES;
+constexpr size_t ST_BYTES = ST_WF_BYTES + ST_SROW_BYTES + ST_INT_BYTES + ST_PART_BYTES;
 constexpr int ST_MAX_DEVICES = 64;
 }  // namespace
 static __device__ __align__(256) unsigned char scratch[ST_BYTES];
@@ -1486,20 +1502,18 @@ del_status del_spec_sample_static(const float* q_logits, const float* p_logits, 
   SampRow* rows_q = reinterpret_cast<SampRow*>(reinterpret_cast<char*>(base) + ST_WF_BYTES);
   SampRow* rows_p = rows_q + STATIC_MAX_GAMMA;
   int* ints = reinterpret_cast<int*>(reinterpret_cast<char*>(base) + ST_WF_BYTES + ST_SROW_BYTES);
-  int* state = ints;          // [0] KV length, [1] pending token: the acceptance kernel adds to [0]
-  int* drafts = ints + 4;     // [STATIC_MAX_GAMMA]
+  int* drafts = ints;         // [STATIC_MAX_GAMMA]
   const int64_t ldw = STATIC_MAX_VOCAB;
-  // the array keeps the last call's contents: what must start at zero is cleared by a kernel (a caller
-  // may be capturing this stream into a graph, where memset nodes are not to be used)
-  if (launch_set_state(state, 0, 0, nullptr, 0, s) != hipSuccess) return DEL_E_DEVICE;
-  if (gamma > 0 && launch_samp_rowstats(q_logits, ld_logits, vocab, gamma, temperature, top_p, wf_q, ldw, rows_q,
-                                        uniforms, drafts, nullptr, nullptr, s) != hipSuccess)
-    return DEL_E_DEVICE;
-  if (launch_samp_rowstats(p_logits, ld_logits, vocab, gamma + 1, temperature, top_p, wf_p, ldw, rows_p, nullptr,
-                           nullptr, nullptr, nullptr, s) != hipSuccess)
+  // (nothing in the array has to start at zero: every call writes what it reads)
+  SampSegs sg{};
+  sg.seg[0].Z = q_logits; sg.seg[0].WF = wf_q; sg.seg[0].rows = rows_q; sg.seg[0].n = gamma;
+  sg.seg[0].draw_r = uniforms; sg.seg[0].draw_tok = drafts;
+  sg.seg[1].Z = p_logits; sg.seg[1].WF = wf_p; sg.seg[1].rows = rows_p; sg.seg[1].n = gamma + 1;
+  if (launch_samp_rowstats(sg, ld_logits, ldw, vocab, temperature, top_p, reinterpret_cast<char*>(ints) + ST_INT_BYTES, s) !=
+      hipSuccess)
     return DEL_E_DEVICE;
   if (launch_samp_accept(q_logits, wf_q, rows_q, p_logits, wf_p, rows_p, ld_logits, ldw, vocab, gamma, drafts,
-                         uniforms + gamma, uniforms + 2 * gamma, state, nullptr, 0, out, s) != hipSuccess)
+                         uniforms + gamma, uniforms + 2 * gamma, nullptr, nullptr, 0, out, s) != hipSuccess)
     return DEL_E_DEVICE;
   return DEL_OK;
 }

@@ -191,12 +191,24 @@ struct SampRow {
   float conf;                    // soft-max probability of the greedy token at temperature 1 (if asked for)
   int pad;
 };
+// Up to two groups of logits rows that one call takes (drafts and targets).
 // draw_r (optional): also draw one token per row with the uniform number draw_r[row] into draw_tok[row]
 // (and into *pending, if given; one row only).
 // conf_out (optional): the greedy token's temperature-1 soft-max probability per row.
-hipError_t launch_samp_rowstats(const float* Z, int64_t ldz, int V, int rows, double temperature, double top_p,
-                                unsigned long long* WF, int64_t ldw, SampRow* out, const float* draw_r, int* draw_tok,
-                                int* pending, float* conf_out, hipStream_t s);
+struct SampSeg {
+  const float* Z;              // [n][ldz]
+  unsigned long long* WF;      // [n][ldw]
+  SampRow* rows;               // [n]
+  const float* draw_r; int* draw_tok; int* pending;
+  float* conf_out;
+  int n;
+};
+struct SampSegs { SampSeg seg[2]; };
+constexpr int SAMP_PARTS = 16;            // work-groups a row is shared by at most
+constexpr int SAMP_PART_BYTES = 4352;     // scratch of one of them
+// scratch: device memory, SAMP_PARTS * SAMP_PART_BYTES per row of both groups.
+hipError_t launch_samp_rowstats(const SampSegs& segs, int64_t ldz, int64_t ldw, int V, double temperature, double top_p,
+                                void* scratch, hipStream_t s);
 hipError_t launch_samp_accept(const float* Zq, const unsigned long long* WFq, const SampRow* rq, const float* Zp,
                               const unsigned long long* WFp, const SampRow* rp, int64_t ldz, int64_t ldw, int V,
                               int gamma, const int* drafts, const float* unif_accept, const float* unif_last, int* state,

@@ -23,6 +23,7 @@ namespace {
 constexpr int SB = 1024;                       // threads of every kernel in this file
 constexpr double FIX = 17592186044416.0;       // 2^44
 constexpr int SWD = 16;                        // loads a thread keeps in flight in a sweep
+constexpr int CAND = 4096;                     // tokens of the nucleus cut's bin that are kept in LDS
 
 typedef unsigned long long u64;
 
@@ -90,43 +91,109 @@ struct PickLds {
   int found;
 };
 
-// Four masses of ids j..j+3 (j a multiple of 4) of a row restricted to its nucleus.
+// Where a draw takes its masses from: PU groups of four ids (j, j + 256, ..., j a multiple of 4) per lane and step.
+// Most ids are outside the nucleus of a peaked row and their weights are not read: the logits of all groups are asked
+// for at once, then the weights of those groups in which the wave has a token of the nucleus.
+constexpr int PU = 4;
+__device__ __forceinline__ void load4(const float* z, int j, int V, float* v) {
+  if (j + 3 < V) {
+    const float4 a = *reinterpret_cast<const float4*>(z + j);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = j + k < V ? z[j + k] : 0.f;
+  }
+}
+__device__ __forceinline__ void load4(const u64* w, int j, int V, u64* m) {
+  if (j + 3 < V) {
+    const ulonglong2 a = *reinterpret_cast<const ulonglong2*>(w + j), b = *reinterpret_cast<const ulonglong2*>(w + j + 2);
+    m[0] = a.x; m[1] = a.y; m[2] = b.x; m[3] = b.y;
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) m[k] = j + k < V ? w[j + k] : 0ull;
+  }
+}
+__device__ __forceinline__ bool kept_any(const SampRow& R, const float* v, int j, int V, bool* in) {
+  bool any = false;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    in[k] = j + k < V && kept(R, v[k], j + k);
+    any |= in[k];
+  }
+  return __any(any);
+}
+
+// The masses of a row restricted to its nucleus.
 struct KeptMass {
   const float* z; const u64* wf; SampRow R; int V;
-  __device__ __forceinline__ void operator()(int j, u64* m) const {
-    if (j + 3 < V) {
-      const float4 zz = *reinterpret_cast<const float4*>(z + j);
-      const ulonglong2 a = *reinterpret_cast<const ulonglong2*>(wf + j);
-      const ulonglong2 b = *reinterpret_cast<const ulonglong2*>(wf + j + 2);
-      m[0] = kept(R, zz.x, j) ? a.x : 0ull;
-      m[1] = kept(R, zz.y, j + 1) ? a.y : 0ull;
-      m[2] = kept(R, zz.z, j + 2) ? b.x : 0ull;
-      m[3] = kept(R, zz.w, j + 3) ? b.y : 0ull;
-    } else {
+  template <int N>
+  __device__ __forceinline__ void masses(int j0, u64 (&m)[N][4]) const {
+    float v[N][4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) m[k] = (j + k < V && kept(R, z[j + k], j + k)) ? wf[j + k] : 0ull;
+    for (int i = 0; i < N; ++i) load4(z, j0 + 256 * i, V, v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      bool in[4];
+      m[i][0] = m[i][1] = m[i][2] = m[i][3] = 0ull;
+      if (kept_any(R, v[i], j0 + 256 * i, V, in)) {
+        u64 w[4];
+        load4(wf, j0 + 256 * i, V, w);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) m[i][k] = in[k] ? w[k] : 0ull;
+      }
+    }
+  }
+};
+
+// max(0, p - q), renormalised rows, in 2^-44: only tokens of p's nucleus have any.
+struct ResidualMass {
+  KeptMass p, q;
+  double ip, iq;
+  template <int N>
+  __device__ __forceinline__ void masses(int j0, u64 (&m)[N][4]) const {
+    float v[N][4];
+#pragma unroll
+    for (int i = 0; i < N; ++i) load4(p.z, j0 + 256 * i, p.V, v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int j = j0 + 256 * i;
+      bool in[4];
+      m[i][0] = m[i][1] = m[i][2] = m[i][3] = 0ull;
+      if (kept_any(p.R, v[i], j, p.V, in)) {
+        float vq[4];
+        u64 a[4], b[4];
+        load4(p.wf, j, p.V, a);
+        load4(q.z, j, p.V, vq);
+        load4(q.wf, j, p.V, b);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (in[k]) {
+            const double d = (double)a[k] * ip - (double)(kept(q.R, vq[k], j + k) ? b[k] : 0ull) * iq;
+            m[i][k] = d > 0.0 ? (u64)rint(d * FIX) : 0ull;
+          }
+      }
     }
   }
 };
 
 // Draw by inverse cumulative mass in id order: the first id whose cumulative mass exceeds
-// floor(r * total).  mass4(j, m) gives the masses of ids j..j+3.  Each wave owns a contiguous
-// segment of the ids, 256 per step (4 per lane, 16-byte loads): first every wave sums its segment,
-// then the wave whose segment holds the target walks it again with a wave scan per step.
+// floor(r * total).  Each wave owns a contiguous segment of the ids, 256 per group (4 per lane, 16-byte loads):
+// first every wave sums its segment, then the wave whose segment holds the target walks it again with a wave
+// scan per group.
 // Every thread returns the id (-1 if the total is 0); *total_out receives the total mass.
 template <typename F>
-__device__ int pick_by_fraction(const F& mass4, int V, double r, PickLds* L, u64* total_out) {
+__device__ int pick_by_fraction(const F& f, int V, double r, PickLds* L, u64* total_out) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   constexpr int NW = SB / 64;
   const int S = ((V + NW - 1) / NW + 255) & ~255;     // ids per wave, a multiple of 256
   const int s0 = min(V, w * S), s1 = min(V, s0 + S);
   u64 part = 0;
-  for (int base = s0; base < s1; base += 512) {
-    u64 m[8];
-    mass4(base + 4 * lane, m);
-    if (base + 256 < s1) mass4(base + 256 + 4 * lane, m + 4);
-    else m[4] = m[5] = m[6] = m[7] = 0;
-    part += ((m[0] + m[1]) + (m[2] + m[3])) + ((m[4] + m[5]) + (m[6] + m[7]));
+  for (int base = s0; base < s1; base += 256 * PU) {
+    u64 m[PU][4];
+    f.masses(base + 4 * lane, m);
+#pragma unroll
+    for (int i = 0; i < PU; ++i)
+      if (base + 256 * i < s1) part += (m[i][0] + m[i][1]) + (m[i][2] + m[i][3]);
   }
   for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
   if (lane == 0) L->wtot[w] = part;
@@ -143,35 +210,42 @@ __device__ int pick_by_fraction(const F& mass4, int V, double r, PickLds* L, u64
   for (int i = 0; i < w; ++i) excl += L->wtot[i];
   if (part > 0 && excl <= target && target < excl + part) {   // this wave's segment holds the target
     u64 run = excl;
-    for (int base = s0; base < s1; base += 256) {
-      u64 m[4];
-      mass4(base + 4 * lane, m);
-      const u64 g = (m[0] + m[1]) + (m[2] + m[3]);
-      u64 inc = g;
-      for (int off = 1; off < 64; off <<= 1) {
-        const u64 o = __shfl_up(inc, off, 64);
-        if (lane >= off) inc += o;
-      }
-      const unsigned long long hit = __ballot(run + inc > target);
-      if (hit) {
-        if (lane == __ffsll((long long)hit) - 1) {
-          u64 c = run + inc - g;
-          int k = 0;
-          for (; k < 3; ++k) {
-            c += m[k];
-            if (c > target) break;
-          }
-          L->found = base + 4 * lane + k;
+    bool done = false;
+    for (int base = s0; base < s1 && !done; base += 256 * PU) {
+      u64 m[PU][4];
+      f.masses(base + 4 * lane, m);
+#pragma unroll
+      for (int i = 0; i < PU; ++i) {
+        if (done || base + 256 * i >= s1) break;              // uniform
+        const u64 g = (m[i][0] + m[i][1]) + (m[i][2] + m[i][3]);
+        if (!__any(g != 0)) continue;                         // the running mass does not move
+        u64 inc = g;
+        for (int off = 1; off < 64; off <<= 1) {
+          const u64 o = __shfl_up(inc, off, 64);
+          if (lane >= off) inc += o;
         }
-        break;
+        const unsigned long long hit = __ballot(run + inc > target);
+        if (hit) {
+          if (lane == __ffsll((long long)hit) - 1) {
+            u64 c = run + inc - g;
+            int k = 0;
+            for (; k < 3; ++k) {
+              c += m[i][k];
+              if (c > target) break;
+            }
+            L->found = base + 256 * i + 4 * lane + k;
+          }
+          done = true;
+          break;
+        }
+        run += __shfl(inc, 63, 64);
       }
-      run += __shfl(inc, 63, 64);
     }
   }
   __syncthreads();
-  const int f = L->found;
+  const int found = L->found;
   __syncthreads();
-  return f;
+  return found;
 }
 
 // The first bin, in scan order, at which `above` plus the bins' running mass reaches `target`; scan
@@ -210,26 +284,47 @@ __device__ __forceinline__ void select_bin(const u64* hist, u64 above, u64 targe
 
 }  // namespace
 
-// One block per logits row: maximum, greedy token, its temperature-1 soft-max probability, the
-// fixed-point weights of all tokens, and the nucleus (threshold key, tie cut, kept mass).  With
-// draw_r: also draws a token from the row's nucleus with the uniform number draw_r[row] into
-// draw_tok[row] (and into *pending, if given).
-__global__ void __launch_bounds__(SB) samp_rowstats_k(const float* Z, long long ldz, int V, double inv_temp,
-                                                      double top_p, u64* WF, long long ldw, SampRow* rows,
-                                                      const float* draw_r, int* draw_tok, int* pending,
-                                                      float* conf_out) {
-  __shared__ PickLds pl;
-  __shared__ double dbuf[SB];
-  __shared__ u64 hist[256];
+// A logits row becomes a distribution in two kernels.  The fp64 exponentials of a whole row on one CU were two thirds of
+// the time of the single kernel before them (34 us for a row of 32000, whatever the number of rows), so
+//   samp_weights_k  grid (parts, rows): every part finds the row's maximum for itself (the row comes from L2 and a second
+//                   launch for it would cost more), computes the fixed-point weights of its share of the tokens and leaves
+//                   sums and a 256-bin histogram of masses;
+//   samp_select_k   one block per row: adds the parts, finds the nucleus, draws.
+// Both are bound by their chain of dependent steps (load, reduce, scan), not by bytes.  8 draft and 9 target rows of
+// 32000: two launches for all rows, acceptance included 42 us; one block per row and group took 93 us.
+struct SampPartHead { u64 wsum; double s1; float zmax, zmin; int arg, pad; };
+struct SampPart {
+  u64 mass[256];
+  unsigned kmin[256], kmax[256];   // smallest and largest order key of a bin
+  SampPartHead h;
+};
+static_assert(sizeof(SampPart) <= SAMP_PART_BYTES, "the scratch that callers provide");
+
+__device__ __forceinline__ const SampSeg& seg_of(const SampSegs& g, int& row) {
+  const bool second = row >= g.seg[0].n;
+  if (second) row -= g.seg[0].n;
+  return g.seg[second ? 1 : 0];
+}
+
+// Maximum, greedy token, minimum of the row; weights and their sum of this part; on the way the first pass of the nucleus
+// search: 256 bins linear in the logit between the row's maximum (bin 0) and minimum, which spreads the row evenly
+// (the bit patterns of a narrow range would fall into a few bins and serialise the atomics); each bin also records the
+// smallest and largest key it received.
+__global__ void __launch_bounds__(SB) samp_weights_k(SampSegs segs, long long ldz, long long ldw, int V, double inv_temp,
+                                                     int nucleus, SampPart* parts) {
+  __shared__ u64 hist[256], sw[SB / 64];
+  __shared__ double sd[SB / 64];
   __shared__ unsigned bmin[256], bmax[256];
-  __shared__ float s_max, s_min;
-  __shared__ int s_arg, s_sel;
-  __shared__ u64 s_above;
-  u64* sbuf = pl.buf;
-  const int row = blockIdx.x, t = threadIdx.x;
-  const float* z = Z + (long long)row * ldz;
-  u64* wf = WF + (long long)row * ldw;
-  // ---- maximum, the lowest id that attains it, and the minimum
+  __shared__ float smx[SB / 64], smn[SB / 64];
+  __shared__ int sar[SB / 64];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, P = gridDim.x, part = blockIdx.x;
+  SampPart* out = parts + (size_t)blockIdx.y * P + part;
+  int row = blockIdx.y;
+  const SampSeg& sg = seg_of(segs, row);
+  const float* z = sg.Z + (long long)row * ldz;
+  u64* wf = sg.WF + (long long)row * ldw;
+  const bool conf = sg.conf_out != nullptr;
+  if (t < 256) { hist[t] = 0; bmin[t] = 0xffffffffu; bmax[t] = 0u; }
   float mx = -INFINITY, mn = INFINITY;
   int arg = 0x7fffffff;
   sweep(z, V, [&](int j, float zj) {
@@ -237,38 +332,29 @@ __global__ void __launch_bounds__(SB) samp_rowstats_k(const float* Z, long long 
     if (v > mx) { mx = v; arg = j; }
     mn = fminf(mn, v);
   });
-  float* fb = reinterpret_cast<float*>(dbuf);
-  float* fb2 = fb + SB;
-  int* ib = reinterpret_cast<int*>(sbuf);
-  fb[t] = mx; fb2[t] = mn; ib[t] = arg;
-  __syncthreads();
-  for (int off = SB / 2; off > 0; off >>= 1) {
-    if (t < off) {
-      const float o = fb[t + off];
-      const int oi = ib[t + off];
-      if (o > fb[t] || (o == fb[t] && oi < ib[t])) { fb[t] = o; ib[t] = oi; }
-      fb2[t] = fminf(fb2[t], fb2[t + off]);
-    }
-    __syncthreads();
+  for (int o = 32; o > 0; o >>= 1) {
+    const float ov = __shfl_xor(mx, o);
+    const int oi = __shfl_xor(arg, o);
+    if (ov > mx || (ov == mx && oi < arg)) { mx = ov; arg = oi; }
+    mn = fminf(mn, __shfl_xor(mn, o));
   }
-  if (t == 0) { s_max = fb[0]; s_min = fb2[0]; s_arg = ib[0]; }
+  if (lane == 0) { smx[wave] = mx; smn[wave] = mn; sar[wave] = arg; }
   __syncthreads();
-  const float zmax = s_max;
-  const float zmin = s_min;
-  // ---- weights and their total; on the way the first pass of the nucleus search: 256 bins linear
-  //      in the logit between the row's maximum (bin 0) and minimum, which spreads the row evenly
-  //      (the bit patterns of a narrow range would fall into a few bins and serialise the
-  //      atomics); each bin also records the smallest and largest key it received
-  const bool nucleus = top_p < 1.0;
+  float zmax = smx[0], zmin = smn[0];
+  arg = sar[0];
+#pragma unroll
+  for (int w = 1; w < SB / 64; ++w) {
+    if (smx[w] > zmax || (smx[w] == zmax && sar[w] < arg)) { zmax = smx[w]; arg = sar[w]; }
+    zmin = fminf(zmin, smn[w]);
+  }
   const float scale = zmax > zmin ? 256.0f / (zmax - zmin) : 0.0f;
-  if (t < 256) { hist[t] = 0; bmin[t] = 0xffffffffu; bmax[t] = 0u; }
-  __syncthreads();
+  const int C = (V + P - 1) / P, lo = min(V, part * C), hi = min(V, lo + C);
   u64 wsum = 0;
   double s1 = 0.0;   // temperature-1 partition sum, only when the confidence is asked for
-  sweep(z, V, [&](int j, float zj) {
-    const float zc = zj + 0.0f;
+  for (int j = lo + t; j < hi; j += SB) {
+    const float zc = z[j] + 0.0f;
     const double dz = (double)zc - (double)zmax;
-    if (conf_out) s1 += exp(dz);
+    if (conf) s1 += exp(dz);
     const u64 w = (u64)rint(exp(dz * inv_temp) * FIX);
     wf[j] = w;
     wsum += w;
@@ -279,27 +365,59 @@ __global__ void __launch_bounds__(SB) samp_rowstats_k(const float* Z, long long 
       atomicMin(&bmin[b], k);
       atomicMax(&bmax[b], k);
     }
-  });
-  __syncthreads();
-  sbuf[t] = wsum;
-  __syncthreads();
-  for (int off = SB / 2; off > 0; off >>= 1) {
-    if (t < off) sbuf[t] += sbuf[t + off];
-    __syncthreads();
   }
-  const u64 Wtot = sbuf[0];
-  __syncthreads();
-  float conf = 0.f;
-  if (conf_out) {
-    dbuf[t] = s1;
-    __syncthreads();
-    for (int off = SB / 2; off > 0; off >>= 1) {
-      if (t < off) dbuf[t] += dbuf[t + off];
-      __syncthreads();
-    }
-    conf = (float)(1.0 / dbuf[0]);
-    __syncthreads();
+  for (int o = 32; o > 0; o >>= 1) {
+    wsum += __shfl_xor(wsum, o);
+    s1 += __shfl_xor(s1, o);
   }
+  if (lane == 0) { sw[wave] = wsum; sd[wave] = s1; }
+  __syncthreads();
+  if (t < 256) { out->mass[t] = hist[t]; out->kmin[t] = bmin[t]; out->kmax[t] = bmax[t]; }
+  if (t == 0) {
+    u64 W = 0;
+    double D = 0.0;
+    for (int w = 0; w < SB / 64; ++w) { W += sw[w]; D += sd[w]; }
+    out->h = SampPartHead{W, D, zmax, zmin, arg, 0};
+  }
+}
+
+// The nucleus (threshold key, tie cut, kept mass) of one row and its record; with draw_r also a token drawn from the
+// nucleus with the uniform number draw_r[row] into draw_tok[row] (and into *pending, if given).
+__global__ void __launch_bounds__(SB) samp_select_k(SampSegs segs, long long ldz, long long ldw, int V, double top_p, int P,
+                                                    const SampPart* parts) {
+  __shared__ PickLds pl;
+  __shared__ int ibuf[SB];
+  __shared__ u64 hist[256];
+  __shared__ unsigned bmin[256], bmax[256];
+  __shared__ unsigned ckey[CAND];
+  __shared__ int cid[CAND];
+  __shared__ u64 cw[CAND];
+  __shared__ int s_sel, s_cnt;
+  __shared__ u64 s_above;
+  u64* sbuf = pl.buf;
+  const int t = threadIdx.x;
+  const SampPart* pr = parts + (size_t)blockIdx.x * P;
+  int row = blockIdx.x;
+  const SampSeg& sg = seg_of(segs, row);
+  const float* z = sg.Z + (long long)row * ldz;
+  const u64* wf = sg.WF + (long long)row * ldw;
+  const bool nucleus = top_p < 1.0;
+  if (t < 256) {
+    u64 m = 0;
+    unsigned lo = 0xffffffffu, hi = 0u;
+#pragma unroll 4
+    for (int i = 0; i < P; ++i) { m += pr[i].mass[t]; lo = min(lo, pr[i].kmin[t]); hi = max(hi, pr[i].kmax[t]); }
+    hist[t] = m; bmin[t] = lo; bmax[t] = hi;
+  }
+  u64 Wtot = 0;
+  double s1 = 0.0;
+#pragma unroll 4
+  for (int i = 0; i < P; ++i) { Wtot += pr[i].h.wsum; s1 += pr[i].h.s1; }
+  const float zmax = pr[0].h.zmax;
+  const int arg = pr[0].h.arg;
+  const float conf = sg.conf_out ? (float)(1.0 / s1) : 0.f;
+  if (t == 0) s_cnt = 0;
+  __syncthreads();
   unsigned kstar = 0;
   int tie_id = V;
   u64 Wkept = Wtot;
@@ -321,19 +439,38 @@ __global__ void __launch_bounds__(SB) samp_rowstats_k(const float* Z, long long 
     unsigned prefix = khi & mask;
     int n_last = 0, id_last = V;
     u64 w_last = 0;
+    // the tokens of that range, usually a few hundred, go to LDS; a wider range is swept again for every digit
+    sweep(z, V, [&](int j, float zj) {
+      const unsigned k = order_key(zj);
+      if (k >= klo && k <= khi) {
+        const int i = atomicAdd(&s_cnt, 1);
+        if (i < CAND) { ckey[i] = k; cid[i] = j; }
+      }
+    });
+    __syncthreads();
+    const int ncand = s_cnt;
+    if (ncand <= CAND)
+      for (int i = t; i < ncand; i += SB) cw[i] = wf[cid[i]];   // (this thread's own entries in the loops below)
     for (int shift = shift0; shift >= 0; shift = shift >= 8 ? shift - 8 : (shift > 0 ? 0 : -1)) {
       if (t < 256) hist[t] = 0;
       __syncthreads();
       if (shift == 0 && t < 256) { bmin[t] = 0xffffffffu; bmax[t] = 0u; }   // now: lowest id, count
       __syncthreads();
-      sweep_w(z, wf, V, [&](int j, float zj, u64 w) {
-        const unsigned k = order_key(zj);
-        if (k >= klo && k <= khi && (k & mask) == prefix) {
+      auto count = [&](int j, unsigned k, u64 w) {
+        if ((k & mask) == prefix) {
           const unsigned dgt = (k >> shift) & 255u;
           atomicAdd(&hist[dgt], w);
           if (shift == 0) { atomicMin(&bmin[dgt], (unsigned)j); atomicAdd(&bmax[dgt], 1u); }
         }
-      });
+      };
+      if (ncand <= CAND) {
+        for (int i = t; i < ncand; i += SB) count(cid[i], ckey[i], cw[i]);
+      } else {
+        sweep_w(z, wf, V, [&](int j, float zj, u64 w) {
+          const unsigned k = order_key(zj);
+          if (k >= klo && k <= khi) count(j, k, w);
+        });
+      }
       __syncthreads();
       select_bin(hist, above, target, true, &s_sel, &s_above);
       __syncthreads();
@@ -366,7 +503,6 @@ __global__ void __launch_bounds__(SB) samp_rowstats_k(const float* Z, long long 
       w_each = sbuf[0];
       __syncthreads();
       int n_eq;
-      int* ibuf = reinterpret_cast<int*>(dbuf);
       const int excl = block_exscan<int>(cnt, ibuf, &n_eq);
       int need = n_eq;
       if (w_each > 0) {
@@ -387,26 +523,26 @@ __global__ void __launch_bounds__(SB) samp_rowstats_k(const float* Z, long long 
     }
   }
   SampRow R;
-  R.zmax = zmax; R.kstar = kstar; R.tie_id = tie_id; R.argmax = s_arg;
+  R.zmax = zmax; R.kstar = kstar; R.tie_id = tie_id; R.argmax = arg;
   R.Wkept = Wkept; R.Wtot = Wtot; R.conf = conf; R.pad = 0;
   if (t == 0) {
-    rows[row] = R;
-    if (conf_out) conf_out[row] = conf;
+    sg.rows[row] = R;
+    if (sg.conf_out) sg.conf_out[row] = conf;
   }
-  if (draw_r) {
+  if (sg.draw_r) {
     u64 total;
-    const int tok = pick_by_fraction(KeptMass{z, wf, R, V}, V, (double)draw_r[row], &pl, &total);
+    const int tok = pick_by_fraction(KeptMass{z, wf, R, V}, V, (double)sg.draw_r[row], &pl, &total);
     if (t == 0) {
       const int tk = tok >= 0 ? tok : R.argmax;
-      draw_tok[row] = tk;
-      if (pending) *pending = tk;
+      sg.draw_tok[row] = tk;
+      if (sg.pending) *sg.pending = tk;
     }
   }
 }
 
 // Acceptance of gamma drafted tokens and the round's last token; commits the KV length and the
-// pending token.  Rows 0..gamma-1 of (Zq, WFq, rq) are the draft steps, rows 0..gamma of
-// (Zp, WFp, rp) the target's.  unif_accept[0..gamma) decide the acceptances, *unif_last draws the last token.
+// pending token (state may be null: the KV length then counts from 0).  Rows 0..gamma-1 of (Zq, WFq, rq)
+// are the draft steps, rows 0..gamma of (Zp, WFp, rp) the target's.  unif_accept[0..gamma) decide the acceptances, *unif_last draws the last token.
 // result: [0]=u, [1]=new KV length, [2]=last token, [3..3+gamma)=drafts, then the L*m shadow tokens.
 __global__ void __launch_bounds__(SB) samp_accept_k(const float* Zq, const u64* WFq, const SampRow* rq,
                                                     const float* Zp, const u64* WFp, const SampRow* rp,
@@ -449,20 +585,9 @@ __global__ void __launch_bounds__(SB) samp_accept_k(const float* Zq, const u64* 
     const float* zq = Zq + (long long)u * ldz;
     const u64* wq = WFq + (long long)u * ldw;
     const SampRow Q = rq[u];
-    const double ip = 1.0 / (double)P.Wkept, iq = 1.0 / (double)Q.Wkept;
-    const KeptMass mp{zp, wp, P, V}, mq{zq, wq, Q, V};
-    auto res4 = [&](int j, u64* m) {
-      u64 a[4], b[4];
-      mp(j, a);
-      mq(j, b);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const double d = (double)a[k] * ip - (double)b[k] * iq;
-        m[k] = d > 0.0 ? (u64)rint(d * FIX) : 0ull;
-      }
-    };
+    const ResidualMass res{KeptMass{zp, wp, P, V}, KeptMass{zq, wq, Q, V}, 1.0 / (double)P.Wkept, 1.0 / (double)Q.Wkept};
     u64 total;
-    tok = pick_by_fraction(res4, V, r, &pl, &total);
+    tok = pick_by_fraction(res, V, r, &pl, &total);
   }
   if (tok < 0) {
     u64 total;
@@ -470,22 +595,29 @@ __global__ void __launch_bounds__(SB) samp_accept_k(const float* Zq, const u64* 
     if (tok < 0) tok = P.argmax;
   }
   if (t == 0) {
-    const int T = state[0] + u + 1;
-    state[0] = T;
-    state[1] = tok;
+    const int T = (state ? state[0] : 0) + u + 1;
+    if (state) { state[0] = T; state[1] = tok; }
     result[0] = u; result[1] = T; result[2] = tok;
   }
   for (int i = t; i < gamma; i += SB) result[3 + i] = drafts[i];
   for (int i = t; i < n_shadow; i += SB) result[3 + gamma + i] = shadow_ids[i];
 }
 
-hipError_t launch_samp_rowstats(const float* Z, int64_t ldz, int V, int rows, double temperature, double top_p,
-                                unsigned long long* WF, int64_t ldw, SampRow* out, const float* draw_r, int* draw_tok,
-                                int* pending, float* conf_out, hipStream_t s) {
-  if (rows <= 0 || V <= 0 || !(temperature > 0.0) || !(top_p > 0.0) || (draw_r && !draw_tok))
+// Work-groups per row: 2048 tokens each, as many as the scratch of a row holds at most.  (32000 tokens on 16 parts: 4
+// exponentials a thread.)
+static int samp_parts(int V) { return V >= 2048 * SAMP_PARTS ? SAMP_PARTS : (V + 2047) / 2048; }
+
+hipError_t launch_samp_rowstats(const SampSegs& segs, int64_t ldz, int64_t ldw, int V, double temperature, double top_p,
+                                void* scratch, hipStream_t s) {
+  const int rows = segs.seg[0].n + segs.seg[1].n, P = samp_parts(V);
+  if (rows <= 0 || V <= 0 || !(temperature > 0.0) || !(top_p > 0.0) || !scratch || segs.seg[0].n < 0 || segs.seg[1].n < 0)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(samp_rowstats_k, dim3(rows), dim3(SB), 0, s, Z, (long long)ldz, V, 1.0 / temperature, top_p, WF,
-                     (long long)ldw, out, draw_r, draw_tok, pending, conf_out);
+  for (const SampSeg& g : segs.seg)
+    if (g.n > 0 && (!g.Z || !g.WF || !g.rows || (g.draw_r && !g.draw_tok))) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(samp_weights_k, dim3(P, rows), dim3(SB), 0, s, segs, (long long)ldz, (long long)ldw, V, 1.0 / temperature,
+                     top_p < 1.0 ? 1 : 0, (SampPart*)scratch);
+  hipLaunchKernelGGL(samp_select_k, dim3(rows), dim3(SB), 0, s, segs, (long long)ldz, (long long)ldw, V, top_p, P,
+                     (const SampPart*)scratch);
   return hipGetLastError();
 }
 
