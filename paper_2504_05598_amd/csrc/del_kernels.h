@@ -108,9 +108,9 @@ struct AttnP {
 
 hipError_t launch_gemm_valu(const GemmP& p, int epi, int waves, hipStream_t s);
 // Which kernel the two launchers here take for p: the forms with several row blocks per work-group
-// (gemv_rows_k: one row, bf16, 128, 160 or 256 k tiles, at least 256 row blocks; gemm_mfma_rows_k: up to 8 rows, 128
-// or 160 k tiles, or up to 16 rows, 128 k tiles and any epilogue but the residual one; at least 256 row blocks), unless
-// p.rows_form == 1.
+// (gemv_rows_k: one row, bf16, 128, 160 or 256 k tiles, at least 256 row blocks, at most 1536 of 256 k tiles;
+// gemm_mfma_rows_k: up to 8 rows, 128 or 160 k tiles, or up to 16 rows, 128 k tiles and any epilogue but the residual
+// one; at least 256 row blocks), unless p.rows_form == 1.
 bool gemv_rows_applies(const GemmP& p);
 bool gemm_mfma_rows_applies(const GemmP& p, int epi, int col_blocks);
 hipError_t launch_gemm_mfma(const GemmP& p, int epi, int waves, int col_blocks, hipStream_t s);

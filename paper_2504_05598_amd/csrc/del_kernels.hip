@@ -1764,8 +1764,12 @@ static hipError_t launch_valu_k(const GemmP& p, int epi, int waves, hipStream_t 
   return hipErrorInvalidValue;
 }
 
+// (256 k tiles: up to six row blocks per work-group.  One row block per work-group / gemv_rows_k, us: 512 row blocks
+// 30.8 / 28.0, 640 32.1 / 31.0, 2000 82.2 / 84.6, 3584 141.4 / 144.5: with many row blocks the start-up that gemv_rows_k
+// saves no longer counts, and two work-groups per CU keep more requests out.)
 bool gemv_rows_applies(const GemmP& p) {
-  return p.wdtype == 1 && p.M == 1 && p.rows_form != 1 && p.NB >= ROWS_GRID && !p.XsOut && (p.KT == 128 || p.KT == 160 || p.KT == 256);
+  return p.wdtype == 1 && p.M == 1 && p.rows_form != 1 && p.NB >= ROWS_GRID && !p.XsOut &&
+         (p.KT == 128 || p.KT == 160 || (p.KT == 256 && p.NB <= 6 * ROWS_GRID));
 }
 bool gemm_mfma_rows_applies(const GemmP& p, int epi, int col_blocks) {
   // (not with the residual epilogue and separate high and low parts: that instantiation does not fit 128 registers)

@@ -290,7 +290,7 @@ __device__ __forceinline__ void select_bin(const u64* hist, u64 above, u64 targe
 //                   launch for it would cost more), computes the fixed-point weights of its share of the tokens and leaves
 //                   sums and a 256-bin histogram of masses;
 //   samp_select_k   one block per row: adds the parts, finds the nucleus, draws.
-// Both are bound by their chain of dependent steps (load, reduce, scan), not by bytes.  8 draft and 9 target rows of
+// Both are bound by their chain of dependent steps (load, reduce, scan), not by bytes.  4 draft and 5 target rows of
 // 32000: two launches for all rows, acceptance included 42 us; one block per row and group took 93 us.
 struct SampPartHead { u64 wsum; double s1; float zmax, zmin; int arg, pad; };
 struct SampPart {
