@@ -422,7 +422,7 @@ def micro(cfg, DelContext):
         if kt > 480:
             print(f"{name:8s} k tiles {kt} beyond the measurement kernel's limit")
             continue
-        waves = 8 if nb * 8 >= 2 * 3072 else 16   # the library's own choice of waves per row block
+        waves = 8 if nb > 256 else 16   # the library's own choice of waves per row block at these sizes
         mb = nb * kt * 1024
         row = [ctx.gemv_parts_us(nb, kt, waves, parts) for _, parts in cols]
         print(f"{name:8s} {nb:6d} {kt:6d} {waves:5d} {mb / 1e6:7.1f} {mb / ceiling / 1e3:7.2f} " + " ".join(f"{v:28.2f}" for v in row))
