@@ -301,8 +301,12 @@ __device__ __forceinline__ void valu_tile(const uint4& w, int kt, int g, const f
 // (at 16 waves they spilled hundreds of registers).
 template <int M> struct ValuWaves { static constexpr int max = M == 1 ? 16 : 4; };
 
-template <int KPL, int M, int EPI>
+// ATT: the input row is the attention output, still in per-split partials (the output projection of one row).  A form of
+// its own: with both kinds of input row in one kernel a register was spilled, and the wait before its store (for the
+// residual, ahead of the tile requests) cost every launch 1.1 us (7B down projection 19.1 us instead of 17.8).
+template <int KPL, int M, int EPI, bool ATT = false>
 __global__ void __launch_bounds__(64 * ValuWaves<M>::max) gemm_valu_k(GemmP p) {
+  static_assert(!ATT || (M == 1 && EPI == EPI_RESID), "");
   constexpr int TK = 4 * KPL;
   extern __shared__ __align__(16) float xs[];
   __shared__ float red[MAXW][M][16];
@@ -351,12 +355,10 @@ __global__ void __launch_bounds__(64 * ValuWaves<M>::max) gemm_valu_k(GemmP p) {
       }
     }
   };
-  // the output projection's input row may be the attention output, still in per-split partials: those of a thread's first
-  // four features are asked for here, all at once, and merged when the tile requests are out (merged split by split in
-  // a loop ahead of them, each split cost a memory round trip)
-  const bool att = M == 1 && EPI == EPI_RESID && p.att_S > 0;
+  // attention partials: those of a thread's first four features are asked for here, all at once, and merged when the tile
+  // requests are out (merged split by split in a loop ahead of them, each split cost a memory round trip)
   AttReq rq;
-  if (att) att_request(p, tid * 4, rq);
+  if constexpr (ATT) att_request(p, tid * 4, rq);
   else if (M == 1) stage_load(tid * 4);
   // one row: the residual, too, is requested up front (asked for in the epilogue it adds a memory round trip to every
   // launch: 0.8 us of the 5.3 a small matrix takes)
@@ -374,7 +376,7 @@ __global__ void __launch_bounds__(64 * ValuWaves<M>::max) gemm_valu_k(GemmP p) {
   if (M == 1) {
     // four 16-byte pieces per thread and batch: one batch covers 16 floats x threads, i.e. the whole row
     // for every shape but the widest rows on the smaller work-groups
-    if (att) {
+    if constexpr (ATT) {
       for (int k = tid * 4; k < Kp; k += stride) {
         if (k != tid * 4) att_request(p, k, rq);
         const float4 x = att_merge(p, k, rq);
@@ -1687,7 +1689,7 @@ __global__ void __launch_bounds__(1024) gemv_parts_k(const uint4* __restrict__ W
 // ---------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------
-template <int KPL, int M, int EPI>
+template <int KPL, int M, int EPI, bool ATT = false>
 static hipError_t launch_valu_e(const GemmP& p, int waves, hipStream_t s) {
   while (waves > ValuWaves<M>::max) waves >>= 1;
   dim3 grid(p.NB), block(64 * waves);
@@ -1695,16 +1697,16 @@ static hipError_t launch_valu_e(const GemmP& p, int waves, hipStream_t s) {
   if (lds > 48 * 1024) {  // beyond the default dynamic LDS limit: raise it for this kernel (once is enough)
     static size_t raised = 0;
     if (lds > raised) {
-      hipError_t e = hipFuncSetAttribute((const void*)gemm_valu_k<KPL, M, EPI>,
+      hipError_t e = hipFuncSetAttribute((const void*)gemm_valu_k<KPL, M, EPI, ATT>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
       raised = lds;
     }
   }
   if (p.ev_start && p.ev_stop)
-    hipExtLaunchKernelGGL((gemm_valu_k<KPL, M, EPI>), grid, block, (uint32_t)lds, s, p.ev_start, p.ev_stop, 0, p);
+    hipExtLaunchKernelGGL((gemm_valu_k<KPL, M, EPI, ATT>), grid, block, (uint32_t)lds, s, p.ev_start, p.ev_stop, 0, p);
   else
-    hipLaunchKernelGGL((gemm_valu_k<KPL, M, EPI>), grid, block, lds, s, p);
+    hipLaunchKernelGGL((gemm_valu_k<KPL, M, EPI, ATT>), grid, block, lds, s, p);
   return hipGetLastError();
 }
 
@@ -1743,7 +1745,10 @@ template <int KPL, int M>
 static hipError_t launch_valu_m(const GemmP& p, int epi, int waves, hipStream_t s) {
   switch (epi) {
     case EPI_STORE: return launch_valu_e<KPL, M, EPI_STORE>(p, waves, s);
-    case EPI_RESID: return launch_valu_e<KPL, M, EPI_RESID>(p, waves, s);
+    case EPI_RESID:
+      if constexpr (M == 1)
+        if (p.att_S > 0) return launch_valu_e<KPL, 1, EPI_RESID, true>(p, waves, s);
+      return launch_valu_e<KPL, M, EPI_RESID>(p, waves, s);
     case EPI_QKV: return launch_valu_e<KPL, M, EPI_QKV>(p, waves, s);
     case EPI_SWIGLU: return launch_valu_e<KPL, M, EPI_SWIGLU>(p, waves, s);
     case EPI_ARGMAX: return launch_valu_e<KPL, M, EPI_ARGMAX>(p, waves, s);
